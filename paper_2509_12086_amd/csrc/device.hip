@@ -12,7 +12,9 @@
 //                    bit-plane record.  One lane per vector, 64 vectors per
 //                    wave, all lanes on the same segment in lock step.
 //   estimate_kernel  Section 3.2 estimator over packed records, as an FP32
-//                    matrix-core contraction of scaled codes with queries.
+//                    matrix-core contraction of scaled codes with queries: the
+//                    multi-stage scan, and the plain scan of plans of narrow
+//                    segments (the other plain scans are in scan.hip).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -23,7 +25,7 @@
 #include <string>
 #include <type_traits>
 
-#include "plan.hpp"
+#include "launch.hpp"
 
 using saq::SegEntry;
 
@@ -1791,21 +1793,10 @@ __global__ __launch_bounds__(256) void stage_bound_kernel(const float* __restric
 // ---------------------------------------------------------------------------
 // host helpers
 // ---------------------------------------------------------------------------
-saq_status hip_fail(hipError_t e, const char* what) {
-    return saq::fail(SAQ_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
-}
+saq_status hip_fail(hipError_t e, const char* what) { return saq::hip_status(e, what); }
 
-// The plan must be uploaded, and to the current device: its buffer is read
-// by the kernels launched there.
 saq_status check_plan(const saq_plan* p, const char* what = "plan") {
-    if (!p || p->dev == nullptr) return saq::fail(SAQ_EINVAL, std::string(what) + " not uploaded");
-    int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
-    if (dev != p->dev_id)
-        return saq::fail(SAQ_EINVAL, std::string(what) + " uploaded on device " +
-                                         std::to_string(p->dev_id) + ", current device " +
-                                         std::to_string(dev));
-    return SAQ_OK;
+    return saq::check_uploaded(p, what);
 }
 
 const u32x4* dev_Ms(const saq_plan* p) {
@@ -1814,9 +1805,7 @@ const u32x4* dev_Ms(const saq_plan* p) {
 const float* dev_c(const saq_plan* p) {
     return reinterpret_cast<const float*>(static_cast<const char*>(p->dev) + p->layout.off_c);
 }
-const SegEntry* dev_seg(const saq_plan* p) {
-    return reinterpret_cast<const SegEntry*>(static_cast<const char*>(p->dev) + p->layout.off_seg);
-}
+const SegEntry* dev_seg(const saq_plan* p) { return saq::device_segments(p); }
 const float* dev_S(const saq_plan* p) {
     return reinterpret_cast<const float*>(static_cast<const char*>(p->dev) + p->layout.off_S);
 }
@@ -2054,6 +2043,33 @@ saq_status fused_grid(K kernel, size_t lds, int64_t items, unsigned& grid) {
 }
 }  // namespace
 
+namespace saq {
+
+saq_status hip_status(hipError_t e, const char* what) {
+    return fail(SAQ_EDEVICE, std::string(what) + ": " + hipGetErrorString(e));
+}
+
+// The plan must be uploaded, and to the current device: its buffer is read
+// by the kernels launched there.
+saq_status check_uploaded(const saq_plan* p, const char* what) {
+    if (!p || p->dev == nullptr) return fail(SAQ_EINVAL, std::string(what) + " not uploaded");
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    if (dev != p->dev_id)
+        return fail(SAQ_EINVAL, std::string(what) + " uploaded on device " +
+                                    std::to_string(p->dev_id) + ", current device " +
+                                    std::to_string(dev));
+    return SAQ_OK;
+}
+
+saq_status project_queries(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
+                           float* Qp, float* qn2, hipStream_t st) {
+    return launch_project(p, Q, nq, Qp, std::max(p->D_kept, 1), LAYOUT_ROWS, qn2, st,
+                          RefRows{ref, nullptr, 1});
+}
+
+}  // namespace saq
+
 extern "C" {
 
 int64_t saq_plan_device_bytes(const saq_plan* p) { return p ? p->layout.bytes : -1; }
@@ -2278,23 +2294,17 @@ int64_t saq_estimate_workspace_bytes(const saq_plan* p, int32_t nq) {
     // [nq x n_kept] each, then (16-byte aligned) the three-term bf16 split of
     // the queries [nq x query_groups x 3 x 16 bytes]
     const int64_t dk = std::max(p->D_kept, 1);
-    return q * dk * 4 + q * 4 + (8 + 2) * q * std::max(p->n_kept, 1) * 4 + 16 +
-           q * query_groups(int(dk)) * 48 + 512;
+    // (the integer scan's own layout is in scan.hip)
+    return std::max(q * dk * 4 + q * 4 + (8 + 2) * q * std::max(p->n_kept, 1) * 4 + 16 +
+                        q * query_groups(int(dk)) * 48 + 512,
+                    saq::scan_workspace_bytes(p, nq));
 }
 
 }  // extern "C"
 
-static saq_status scan_impl(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
-                            const uint8_t* codes, const float* factors, int64_t n,
-                            int32_t prefix_bits, float* out, void* ws, int64_t ws_bytes,
-                            void* stream) {
-    if (saq_status st = check_plan(p); st != SAQ_OK) return st;
-    if (nq < 0 || n < 0) return saq::fail(SAQ_EINVAL, "bad sizes");
-    if (prefix_bits < 0) return saq::fail(SAQ_EINVAL, "prefix_bits < 0");
-    if (nq == 0 || n == 0) return SAQ_OK;
-    if (!Q || !codes || !factors || !out || !ws) return saq::fail(SAQ_EINVAL, "null buffer");
-    if (ws_bytes < saq_estimate_workspace_bytes(p, nq)) return saq::fail(SAQ_EINVAL, "workspace too small");
-    hipStream_t st = static_cast<hipStream_t>(stream);
+saq_status saq::scan_split(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
+                           const uint8_t* codes, const float* factors, int64_t n, int32_t prefix_bits,
+                           float* out, void* ws, hipStream_t st) {
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
     float* Qp = reinterpret_cast<float*>(base);
     const int dk = std::max(p->D_kept, 1), qg = query_groups(dk);
@@ -2412,26 +2422,6 @@ saq_status saq_estimate_multistage_ref(const saq_plan* p, const float* Q, int32_
     if (!ref && nq > 0 && n > 0) return saq::fail(SAQ_EINVAL, "null reference");
     return multistage_impl(p, Q, nq, ref, codes, factors, n, tau, m, out, stage, ws, ws_bytes,
                            stream);
-}
-
-saq_status saq_estimate_dist_prefix(const saq_plan* p, const float* Q, int32_t nq,
-                                    const uint8_t* codes, const float* factors, int64_t n,
-                                    int32_t prefix_bits, float* out, void* ws, int64_t ws_bytes,
-                                    void* stream) {
-    return scan_impl(p, Q, nq, nullptr, codes, factors, n, prefix_bits, out, ws, ws_bytes, stream);
-}
-
-saq_status saq_estimate_dist(const saq_plan* p, const float* Q, int32_t nq, const uint8_t* codes,
-                             const float* factors, int64_t n, float* out, void* ws,
-                             int64_t ws_bytes, void* stream) {
-    return scan_impl(p, Q, nq, nullptr, codes, factors, n, 0, out, ws, ws_bytes, stream);
-}
-
-saq_status saq_estimate_dist_ref(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
-                                 const uint8_t* codes, const float* factors, int64_t n, float* out,
-                                 void* ws, int64_t ws_bytes, void* stream) {
-    if (!ref && nq > 0 && n > 0) return saq::fail(SAQ_EINVAL, "null reference");
-    return scan_impl(p, Q, nq, ref, codes, factors, n, 0, out, ws, ws_bytes, stream);
 }
 
 }  // extern "C"

@@ -555,6 +555,18 @@ void saq_plan::derive() {
     // auto mode takes the FP64 totals there
     const int mode = params.projection_accumulation;
     acc64 = mode == 2 || (mode == 0 && (D > 1024 || max_kept_b >= 8));
+    double most = 0.0;
+    for (int r = 0; r < D_kept; ++r) {
+        const float* row = M.data() + int64_t(r) * D;
+        double a[8] = {};                // independent sums, so that the loop vectorises
+        int k = 0;
+        for (; k + 8 <= D; k += 8)
+            for (int e = 0; e < 8; ++e) a[e] += double(row[k + e]) * row[k + e];
+        for (; k < D; ++k) a[0] += double(row[k]) * row[k];
+        most = std::max(most, ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
+    }
+    m_exp = 0;
+    if (most > 0.0 && std::isfinite(most)) (void)std::frexp(std::sqrt(most) * (1.0 + 1.0 / 512), &m_exp);
     build_staging(*this);
 }
 

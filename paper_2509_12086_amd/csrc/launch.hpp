@@ -1,0 +1,35 @@
+// Launch helpers that the device translation units of libsaq.so share.  Not
+// part of the public ABI.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "plan.hpp"
+
+namespace saq {
+
+// The plan must be uploaded, and to the current device.
+saq_status check_uploaded(const saq_plan* p, const char* what);
+saq_status hip_status(hipError_t e, const char* what);
+
+inline const SegEntry* device_segments(const saq_plan* p) {
+    return reinterpret_cast<const SegEntry*>(static_cast<const char*>(p->dev) + p->layout.off_seg);
+}
+
+// Projected queries Qp [nq x max(D_kept, 1)] and ||q - c||^2 [nq], against
+// the plan's c or, when ref is given, against that one row.
+saq_status project_queries(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
+                           float* Qp, float* qn2, hipStream_t st);
+
+// The plain scan on split bf16 operands (device.hip), for checked arguments and
+// a workspace of saq_estimate_workspace_bytes.
+saq_status scan_split(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
+                      const uint8_t* codes, const float* factors, int64_t n, int32_t prefix_bits,
+                      float* out, void* ws, hipStream_t st);
+
+// Device scratch of the integer scan for nq queries (scan.hip).
+int64_t scan_workspace_bytes(const saq_plan* p, int32_t nq);
+
+}  // namespace saq

@@ -61,6 +61,8 @@ struct saq_plan {
     // derived
     int32_t D_kept = 0, n_kept = 0, max_kept_w = 0, max_kept_b = 0;
     bool acc64 = false;                  // projection accumulates k-tiles into FP64
+    int m_exp = 0;                       // every row of M has a norm below 2^m_exp, with a
+                                         // 2^-9 margin for the projection's rounding
     int64_t code_bytes = 0;
     std::vector<saq::SegEntry> kept;
 

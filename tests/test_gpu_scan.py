@@ -1,0 +1,99 @@
+"""The plain scan's integer passes against the oracle's estimator, at the sizes
+where they can go wrong: segment widths around the 64-dim step, the 384-dim
+fold and the byte span of one fetch, 1 to 16 bits (one and several groups of
+planes), prefixes, query counts around the 16-query kernel and the 32- and
+64-query tiles, record counts around the 32- and 128-record tiles, and code
+buffers at every alignment.
+
+Records are given, not encoded: random codes and factors, the norm that of
+f_s u_s.  c = 0 and M = identity rows, so the projected queries are exact.
+Tolerance, in units of ||o||^2 + ||q||^2 (which bounds 2 |<o, q>|): every
+FP32 operation on the inner product rounds by 2^-24 of at most that; a pass
+takes 4 and adds one, the final sum 4, and the queries' fixed point (2^-31 of
+the largest component) less than one more: (5 passes + 5) 2^-24.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2509_12086_amd as saq
+from gpu_util import say, to_dev
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _case(widths, bits, n, nq, seed):
+    rng = np.random.default_rng(seed)
+    D = sum(widths)
+    kept = [(w, b) for w, b in zip(widths, bits) if b > 0]
+    dk = sum(w for w, _ in kept)
+    M = np.eye(D, dtype=np.float32)[:dk]
+    plan = saq.Plan.from_parts(widths, bits, M, np.zeros(D, np.float32)).upload(0)
+    codes = np.concatenate([rng.integers(0, 2 ** b, (n, w)) for w, b in kept], axis=1).astype(np.int32)
+    fac = np.empty((n, len(kept) + 1), np.float32)
+    o2, col = np.zeros(n), 0
+    for s, (w, b) in enumerate(kept):
+        u = codes[:, col:col + w] - (2 ** b - 1) / 2
+        fac[:, s] = rng.lognormal(0.0, 1.0, n) * 2.0 ** -b
+        fac[rng.random(n) < 0.02, s] = 0.0
+        o2 += (fac[:, s].astype(np.float64) ** 2) * (u * u).sum(1)
+        col += w
+    fac[:, -1] = o2
+    Q = (rng.standard_normal((nq, D)) * rng.lognormal(0.0, 1.5, (nq, 1))).astype(np.float32)
+    return plan, codes, oracle.pack(codes, plan.kept_widths, plan.kept_bits), fac, Q
+
+
+def _check(plan, codes, packed, fac, Q, prefix=0, shift=0, label=""):
+    n = len(packed)
+    buf = torch.empty(packed.size + 64, dtype=torch.uint8, device="cuda:0")
+    dev = buf[shift:shift + packed.size].view(n, -1)
+    dev.copy_(to_dev(packed))
+    got = saq.estimate_dist(plan, to_dev(Q), dev, to_dev(fac), prefix_bits=prefix)
+    torch.cuda.synchronize()
+    f64 = fac.astype(np.float64)
+    M, c, _ = plan.arrays()
+    ref = oracle.estimate(Q, M, c, plan.kept_widths, plan.kept_bits, codes, f64[:, :-1], f64[:, -1],
+                          prefix_bits=prefix)
+    scale = f64[:, -1][None, :] + (Q.astype(np.float64) ** 2).sum(1)[:, None]
+    # groups of planes (at most 8; fewer in wide segments) times runs of 384 dims
+    passes = sum(-(-b // max(1, min(8, 1 + (241 - min(48, 8 * -(-w // 64))) // -(-w // 8)))) * -(-w // 384)
+                 for w, b in zip(plan.kept_widths, plan.kept_bits))
+    err = np.max(np.abs(got.cpu().numpy() - ref) / scale)
+    say(f"  {label}: nq={len(Q)} n={n} passes={passes} error {err * 2 ** 24:.2f} x 2^-24")
+    assert err <= (5 * passes + 5) * 2.0 ** -24
+
+
+SHAPES = [
+    ([1], [1]), ([7, 9], [16, 3]), ([63, 64, 65], [9, 8, 7]), ([127, 128, 129], [5, 8, 1]),
+    ([16] * 6 + [5], [9, 7, 6, 5, 3, 2, 0]), ([304, 256, 272], [9, 8, 7]), ([384, 385], [8, 4]),
+    ([512, 448], [9, 16]), ([700, 33], [8, 10]), ([2100], [3]), ([8] * 130, [3, 8] * 65),
+]
+
+
+@pytest.mark.parametrize("widths,bits", SHAPES)
+def test_scan_shapes(widths, bits):
+    for nq, n in ((1, 300), (40, 161), (67, 129)):
+        _check(*_case(widths, bits, n, nq, 7 * nq + len(widths)), label=f"W {widths[:6]} B {bits[:6]}")
+
+
+@pytest.mark.parametrize("nq", [1, 2, 15, 16, 17, 31, 32, 33, 63, 64, 65, 130])
+def test_scan_query_counts(nq):
+    _check(*_case([80, 30], [9, 4], 200, nq, nq), label="queries")
+    _check(*_case([144, 144, 60], [8, 6, 3], 140, nq, nq), label="queries, longer records")
+
+
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 127, 128, 129, 130, 255, 256, 257, 1025])
+def test_scan_record_counts_and_alignments(n):
+    # 1 to 3 code bytes: whole buffers shorter than a 16-byte load
+    for widths, bits in (([4], [1]), ([3, 9], [2, 1]), ([50, 70], [5, 8])):
+        for nq in (3, 35):
+            case = _case(widths, bits, n, nq, n)
+            for shift in (0, 1, 6, 16):
+                _check(*case, shift=shift, label=f"shift {shift}")
+
+
+@pytest.mark.parametrize("prefix", [1, 2, 7, 8, 9, 15, 16])
+def test_scan_prefixes(prefix):
+    for nq in (2, 50):
+        _check(*_case([70, 64, 300], [16, 9, 8], 150, nq, prefix), prefix=prefix, label=f"prefix {prefix}")
