@@ -17,6 +17,7 @@ ARCH = os.environ.get("SAQ_OFFLOAD_ARCH", "gfx950")
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-munsafe-fp-atomics", "-Wall", "-Wno-unused-function"]
+HIP_UNITS = ["device", "fit", "scan", "quantize_few"]
 HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-fopenmp", "-Wall", "-ffp-contract=off"]
 
 
@@ -36,15 +37,14 @@ def hipcc() -> str:
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD, exist_ok=True)
     host_o = os.path.join(BUILD, "host.o")
-    dev_o = os.path.join(BUILD, "device.o")
-    fit_o = os.path.join(BUILD, "fit.o")
-    scan_o = os.path.join(BUILD, "scan.o")
     _run(["g++", *HOST_FLAGS, "-c", os.path.join(CSRC, "host.cpp"), "-o", host_o])
-    _run([hipcc(), *HIP_FLAGS, "-c", os.path.join(CSRC, "device.hip"), "-o", dev_o])
-    _run([hipcc(), *HIP_FLAGS, "-c", os.path.join(CSRC, "fit.hip"), "-o", fit_o])
-    _run([hipcc(), *HIP_FLAGS, "-c", os.path.join(CSRC, "scan.hip"), "-o", scan_o])
+    objects = [host_o]
+    for unit in HIP_UNITS:
+        obj = os.path.join(BUILD, unit + ".o")
+        _run([hipcc(), *HIP_FLAGS, "-c", os.path.join(CSRC, unit + ".hip"), "-o", obj])
+        objects.append(obj)
     tmp = LIB + ".tmp"
-    _run([hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", host_o, dev_o, fit_o, scan_o, "-o", tmp,
+    _run([hipcc(), "-shared", "-fPIC", f"--offload-arch={ARCH}", *objects, "-o", tmp,
           "-lgomp"])
     os.replace(tmp, LIB)
     return LIB

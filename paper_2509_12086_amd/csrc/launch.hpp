@@ -23,6 +23,22 @@ inline const SegEntry* device_segments(const saq_plan* p) {
 saq_status project_queries(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
                            float* Qp, float* qn2, hipStream_t st);
 
+// One dataset's projected rows to quantize, adjust and pack.
+struct QuantItem {
+    const float* O;             // projected rows, leading dimension ld, in `layout`
+    int64_t ld, n;
+    const SegEntry* segs;       // device
+    const float* norm2;
+    uint8_t* codes;
+    float* factors;
+    int64_t code_bytes;
+    int32_t layout, n_kept, dk, max_w;
+};
+// Whether the items are few enough for one wave per vector and segment, and
+// that launch (quantize_few.hip).
+bool few_vectors(const QuantItem* items, int count);
+saq_status launch_quantize_few(const QuantItem* items, int count, int rounds, hipStream_t st);
+
 // The plain scan on split bf16 operands (device.hip), for checked arguments and
 // a workspace of saq_estimate_workspace_bytes.
 saq_status scan_split(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
