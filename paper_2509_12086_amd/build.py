@@ -17,7 +17,7 @@ ARCH = os.environ.get("SAQ_OFFLOAD_ARCH", "gfx950")
 HIP_FLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-munsafe-fp-atomics", "-Wall", "-Wno-unused-function"]
-HIP_UNITS = ["device", "fit", "scan", "quantize_few"]
+HIP_UNITS = ["device", "fit", "scan", "project_few", "quantize_few"]
 HOST_FLAGS = ["-O3", "-std=c++17", "-fPIC", "-fopenmp", "-Wall", "-ffp-contract=off"]
 
 

@@ -25,21 +25,14 @@
 #include <string>
 #include <type_traits>
 
+#include "gemm_common.hpp"
 #include "launch.hpp"
 
 using saq::SegEntry;
 
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
 namespace {
 
-constexpr int TN = saq::kGemmTileN;   // 128 kept dims per tile
 constexpr int NXCD = 8;               // MI355X: 8 XCDs, workgroups dealt round-robin
-
-enum { LAYOUT_ROWS = 0, LAYOUT_DIMS = 1, LAYOUT_TILES = 2 };
 
 // ---------------------------------------------------------------------------
 // Projection GEMM.  Workgroup = 256 threads (4 waves) computes a (64 BI) x 128
@@ -57,46 +50,6 @@ enum { LAYOUT_ROWS = 0, LAYOUT_DIMS = 1, LAYOUT_TILES = 2 };
 // at the same speed).
 // ---------------------------------------------------------------------------
 template <int BI> constexpr int gemm_rows() { return 64 * BI; }
-
-// Per-record reference vectors (Section 3.1's c; the IVF centroid of each
-// record's list in the paper's experiments): record i is centered on row
-// ids[i] of refs [K x D] (all records on row 0 when ids is null) instead of
-// the plan's c.  A record whose id is outside [0, K) is centered on row 0 and
-// gets a NaN norm, so its factors show it.
-struct RefRows {
-    const float* refs;   // null: the plan's c
-    const int32_t* ids;
-    int32_t K;
-};
-
-// Stores rows row .. row+3 of column col of O in the output layout.
-template <int LAYOUT>
-__device__ __forceinline__ void store_quad(float* __restrict__ O, int64_t ld, int64_t n, int64_t row,
-                                           int col, float v0, float v1, float v2, float v3) {
-    if (LAYOUT == LAYOUT_TILES) {
-        // whole 64-row tiles: rows of the last tile past n (copies of row
-        // n-1) are stored too
-        if (row < ((n + 63) & ~int64_t(63))) {
-            float* dst = O + ((row >> 6) * ld + col) * 64 + (row & 63);
-            *reinterpret_cast<float4*>(dst) = make_float4(v0, v1, v2, v3);
-        }
-    } else if (LAYOUT == LAYOUT_DIMS) {
-        float* dst = O + int64_t(col) * ld + row;
-        if (row + 3 < n) {
-            *reinterpret_cast<float4*>(dst) = make_float4(v0, v1, v2, v3);
-        } else {
-            if (row + 0 < n) dst[0] = v0;
-            if (row + 1 < n) dst[1] = v1;
-            if (row + 2 < n) dst[2] = v2;
-            if (row + 3 < n) dst[3] = v3;
-        }
-    } else {
-        if (row + 0 < n) O[(row + 0) * ld + col] = v0;
-        if (row + 1 < n) O[(row + 1) * ld + col] = v1;
-        if (row + 2 < n) O[(row + 2) * ld + col] = v2;
-        if (row + 3 < n) O[(row + 3) * ld + col] = v3;
-    }
-}
 
 // ---------------------------------------------------------------------------
 // Split-operand projection.  Every FP32 operand a is written exactly as
@@ -136,25 +89,7 @@ __device__ __forceinline__ void store_quad(float* __restrict__ O, int64_t ld, in
 // compute unit (two with per-row references, whose extra c registers would
 // spill at three); FP64 totals run two.
 // ---------------------------------------------------------------------------
-constexpr int SK = saq::kSplitK;              // input dims per k-step
-constexpr int SCB = saq::kSplitChunks;        // B chunks per buffer
 template <int BI> constexpr int split_lds_floats() { return 2 * (6 * 64 * BI + SCB) * 4; }
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
-    const bf16x2 v = {static_cast<__bf16>(a), static_cast<__bf16>(b)};
-    return __builtin_bit_cast(uint32_t, v);
-}
-// (a, b) -> three packed bf16 pairs, a = a0 + a1 + a2 exactly (normal a)
-__device__ __forceinline__ void split3(float a, float b, uint32_t& h0, uint32_t& h1, uint32_t& h2) {
-    h0 = pack_bf16x2(a, b);
-    const float ra = a - __uint_as_float(h0 << 16), rb = b - __uint_as_float(h0 & 0xffff0000u);
-    h1 = pack_bf16x2(ra, rb);
-    h2 = pack_bf16x2(ra - __uint_as_float(h1 << 16), rb - __uint_as_float(h1 & 0xffff0000u));
-}
-__device__ __forceinline__ floatx16 mfma_bf16(u32x4 a, u32x4 b, floatx16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
 
 // lds: split_lds_floats<BI>() floats, free on entry; on return free except
 // after a NORM tile (the norm hand-off leaves a barrier-protected write).
@@ -1824,7 +1759,17 @@ int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
 saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O, int64_t ld,
                           int layout, float* norm2, hipStream_t st,
-                          RefRows R = RefRows{nullptr, nullptr, 0}) {
+                          RefRows R = RefRows{nullptr, nullptr, 0}, bool fill = true) {
+    if (layout == LAYOUT_DIMS && ((reinterpret_cast<uintptr_t>(O) & 15) != 0 || (ld % 4) != 0))
+        return saq::fail(SAQ_EINVAL, "dims-major output needs a 16-byte aligned buffer and ld % 4 == 0");
+    if (layout == LAYOUT_TILES && (reinterpret_cast<uintptr_t>(O) & 15) != 0)
+        return saq::fail(SAQ_EINVAL, "tiled output needs a 16-byte aligned buffer");
+    if (R.refs != nullptr && layout == LAYOUT_DIMS)
+        return saq::fail(SAQ_EUNSUPPORTED, "per-row references with the dims-major layout");
+    const saq::ProjectItem item{X, n, dev_Ms(p), dev_c(p), R.refs, R.ids, O, ld, norm2, p->D,
+                                p->layout.k_pad, p->D_kept, R.K, p->acc64,
+                                fill && layout == LAYOUT_TILES};
+    if (saq::few_rows(&item, 1)) return saq::launch_project_few(&item, 1, layout, st);
     const int rows = p->acc64 ? gemm_rows<gemm_bi<true>()>() : gemm_rows<gemm_bi<false>()>();
     const int tiles_m = int((n + rows - 1) / rows);
     const int tiles_n = p->layout.n_pad / TN;
@@ -1844,10 +1789,6 @@ saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O
     const dim3 grid(unsigned(NXCD * slots));
     const bool vec = (p->D % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0) &&
                      ((reinterpret_cast<uintptr_t>(R.refs) & 15) == 0);
-    if (layout == LAYOUT_DIMS && ((reinterpret_cast<uintptr_t>(O) & 15) != 0 || (ld % 4) != 0))
-        return saq::fail(SAQ_EINVAL, "dims-major output needs a 16-byte aligned buffer and ld % 4 == 0");
-    if (layout == LAYOUT_TILES && (reinterpret_cast<uintptr_t>(O) & 15) != 0)
-        return saq::fail(SAQ_EINVAL, "tiled output needs a 16-byte aligned buffer");
 #define SAQ_LAUNCH_PROJ(V, L, A, F)                                                               \
     hipLaunchKernelGGL((project_kernel<V, L, A, F>), grid, dim3(256), 0, st, X, n, p->D, dev_Ms(p),\
                        p->layout.k_pad, dev_c(p), p->D_kept, O, ld, norm2, tiles_m, tiles_n, R,  \
@@ -1856,8 +1797,6 @@ saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O
     do { if (p->acc64) SAQ_LAUNCH_PROJ(V, L, true, F); else SAQ_LAUNCH_PROJ(V, L, false, F); } while (0)
     // references per row exist for the tiled (encode) and row (query) layouts
     const bool ref = R.refs != nullptr;
-    if (ref && layout == LAYOUT_DIMS)
-        return saq::fail(SAQ_EUNSUPPORTED, "per-row references with the dims-major layout");
     if (layout == LAYOUT_TILES) {
         if (ref) {
             if (vec) SAQ_LAUNCH_PROJ2(true, LAYOUT_TILES, true); else SAQ_LAUNCH_PROJ2(false, LAYOUT_TILES, true);
@@ -1926,6 +1865,8 @@ int64_t enc_o_bytes(const saq_plan* p, int64_t n) {
 
 
 struct BatchPlan {
+    saq::ProjectItem rows[BATCH_MAX];
+    bool few_rows = false;    // grouped: one workgroup per 32 x 32 block of the projection
     saq::QuantItem item[BATCH_MAX];
     bool few = false;         // grouped: few vectors, one wave per vector and segment
     GemmArgs g{};
@@ -2034,6 +1975,8 @@ saq_status plan_batch(const saq_batch_item* items, int32_t count, int32_t rounds
         Q.O = O; Q.ld = ld; Q.n = it.n; Q.segs = dev_seg(p); Q.n_kept = p->n_kept; Q.norm2 = nrm;
         Q.codes = it.codes_dev; Q.code_bytes = p->code_bytes; Q.codes_align = codes_align;
         Q.factors = it.factors_dev;
+        B.rows[B.q.count - 1] = saq::ProjectItem{it.X_dev, it.n, G.Ms, G.cp, nullptr, nullptr, O, ld, nrm,
+                                                 p->D, G.k_pad, G.dk, 0, p->acc64, 0};
         B.item[B.q.count - 1] = saq::QuantItem{O, ld, it.n, Q.segs, nrm, it.codes_dev, it.factors_dev,
                                                p->code_bytes, LAYOUT_TILES, p->n_kept, p->D_kept, p->max_kept_w};
         Q.first_block = B.quant_blocks;
@@ -2050,6 +1993,7 @@ saq_status plan_batch(const saq_batch_item* items, int32_t count, int32_t rounds
     B.f.ticket = reinterpret_cast<unsigned long long*>(base + take(8));
     B.f.count = B.g.count;
     B.few = saq::few_vectors(B.item, B.q.count);
+    B.few_rows = saq::few_rows(B.rows, B.q.count);
     B.ws_need = off + 256;
     return SAQ_OK;
 }
@@ -2170,7 +2114,7 @@ static saq_status encode_impl(const saq_plan* p, const float* X, int64_t n, int3
     float* nrm = reinterpret_cast<float*>(base + round_up(enc_o_bytes(p, n), 256));
     // with nothing kept the projection kernel still runs its first column
     // tile (all padding) to produce ||x - c||^2
-    saq_status s = launch_project(p, X, n, O, ld, LAYOUT_TILES, nrm, st, R);
+    saq_status s = launch_project(p, X, n, O, ld, LAYOUT_TILES, nrm, st, R, false);
     if (s != SAQ_OK) return s;
     return launch_quantize(p, O, ld, LAYOUT_TILES, n, nrm, rounds, codes, factors, st);
 }
@@ -2296,7 +2240,9 @@ saq_status saq_encode_batched(const saq_batch_item* items, int32_t count, int32_
     }
     // one instantiation per tile shape: the 64-row one also carries datasets
     // with FP64 k-tile totals, the 128-row one keeps three workgroups per CU
-    if (B.bi == 1)
+    if (B.few_rows) {
+        if (saq_status s = saq::launch_project_few(B.rows, B.q.count, LAYOUT_TILES, st); s != SAQ_OK) return s;
+    } else if (B.bi == 1)
         hipLaunchKernelGGL(grouped_gemm_kernel<true>, dim3(unsigned(B.gemm_blocks)), dim3(256), 0, st, B.g);
     else
         hipLaunchKernelGGL(grouped_gemm_kernel<false>, dim3(unsigned(B.gemm_blocks)), dim3(256), 0, st, B.g);

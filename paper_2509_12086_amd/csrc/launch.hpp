@@ -23,6 +23,25 @@ inline const SegEntry* device_segments(const saq_plan* p) {
 saq_status project_queries(const saq_plan* p, const float* Q, int32_t nq, const float* ref,
                            float* Qp, float* qn2, hipStream_t st);
 
+// One dataset's rows to project.
+struct ProjectItem {
+    const float* X;             // [n x D]
+    int64_t n;
+    const void* M_split;        // device plan
+    const float* c;
+    const float* refs;          // per-row references (null: the plan's c)
+    const int32_t* ref_ids;
+    float* O;
+    int64_t ld;
+    float* norm2;               // null: not wanted
+    int32_t D, k_pad, dk, n_refs;
+    int32_t acc64, fill;        // fill: store the rows of the last 64-row tile past n too
+};
+// Whether the items are few enough for one workgroup per 32 x 32 block of the
+// output, and that launch (project_few.hip); all items with references or none.
+bool few_rows(const ProjectItem* items, int count);
+saq_status launch_project_few(const ProjectItem* items, int count, int layout, hipStream_t st);
+
 // One dataset's projected rows to quantize, adjust and pack.
 struct QuantItem {
     const float* O;             // projected rows, leading dimension ld, in `layout`
