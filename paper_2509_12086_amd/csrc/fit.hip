@@ -20,9 +20,10 @@
 //       the indices form n/2 disjoint pairs (the round-robin tournament
 //       schedule), one plane rotation per pair zeroes that pair's
 //       off-diagonal entry, and the rotations of a round commute, so
-//       A <- J^T A J and V <- V J are applied at once: each thread takes one
-//       2 x 2 block (pair P rows, pair Q columns) of A, B' = R_P^T B R_Q,
-//       from one buffer into the other, and the 2 x 2 block of V in place.
+//       A <- J^T A J is applied at once: each 2 x 2 block (pair P rows, pair
+//       Q columns) of A, B' = R_P^T B R_Q, goes from one buffer into the
+//       other.  The rounds' rotations are kept, and V <- V J is applied for a
+//       whole sweep, its rows being independent.
 //       n - 1 rounds make a sweep; sweeps repeat until the off-diagonal
 //       mass is below FP64 rounding of the diagonal (Jacobi 1846; the
 //       parallel ordering of Brent and Luk 1985; the rotation formulas of
@@ -49,14 +50,35 @@ __device__ __forceinline__ int64_t sample_row(int64_t i, int64_t n, int64_t m) {
     return m == n ? i : (i * n) / m;
 }
 
-__global__ __launch_bounds__(256) void mean_part_kernel(const float* __restrict__ X, int64_t n, int D,
-                                                        int64_t m, double* __restrict__ part) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
+// One lane per column and 4,096-row block.  The sum is one chain in row order
+// (the host's), so what counts is loads in flight: MEAN_AHEAD rows are loaded
+// while the ones before them are added.  65,536 x 960: 1,665 us with one load
+// at a time, 265 us so.
+constexpr int MEAN_AHEAD = 32;
+__global__ __launch_bounds__(64) void mean_part_kernel(const float* __restrict__ X, int64_t n, int D,
+                                                       int64_t m, double* __restrict__ part) {
+    const int k = blockIdx.x * 64 + threadIdx.x;
     const int64_t b = blockIdx.y;
     if (k >= D) return;
     double s = 0.0;
-    const int64_t i1 = std::min<int64_t>(m, (b + 1) * MEAN_ROWS);
-    for (int64_t i = b * MEAN_ROWS; i < i1; ++i) s += double(X[sample_row(i, n, m) * D + k]);
+    const int64_t i0 = b * MEAN_ROWS, i1 = std::min<int64_t>(m, i0 + MEAN_ROWS);
+    float cur[MEAN_AHEAD], nxt[MEAN_AHEAD];
+    auto load = [&](int64_t i, float (&v)[MEAN_AHEAD]) {
+#pragma unroll
+        for (int e = 0; e < MEAN_AHEAD; ++e) v[e] = X[sample_row(std::min(i + e, i1 - 1), n, m) * D + k];
+    };
+    load(i0, cur);
+    int64_t i = i0;
+    for (; i + MEAN_AHEAD <= i1; i += MEAN_AHEAD) {
+        load(std::min(i + MEAN_AHEAD, i1 - 1), nxt);
+#pragma unroll
+        for (int e = 0; e < MEAN_AHEAD; ++e) s += double(cur[e]);
+#pragma unroll
+        for (int e = 0; e < MEAN_AHEAD; ++e) cur[e] = nxt[e];
+    }
+#pragma unroll
+    for (int e = 0; e < MEAN_AHEAD; ++e)
+        if (i + e < i1) s += double(cur[e]);
     part[b * D + k] = s;
 }
 
@@ -218,9 +240,9 @@ __device__ __forceinline__ void jacobi_pair(int N, int r, int k, int& a, int& b)
         a = r;
         b = N - 1;
     } else {
-        const int m = N - 1;
-        a = (r + k) % m;
-        b = (r - k + m) % m;
+        const int m = N - 1;         // 0 <= r < m, 0 < k < m
+        a = r + k < m ? r + k : r + k - m;
+        b = r >= k ? r - k : r - k + m;
     }
     if (a > b) {
         const int t = a;
@@ -250,6 +272,14 @@ __device__ __forceinline__ void jacobi_rotation(double app, double aqq, double a
     s = t * c;
 }
 
+// (x, y) -> (c x - s y, s x + c y).  The roundings are spelled out: the sign
+// and order of the eigenvectors follow from them (a rotation of two nearly
+// equal diagonal entries may turn either way).
+__device__ __forceinline__ void rotate2(double x, double y, double c, double s, double& x1, double& y1) {
+    x1 = fma(c, x, -(s * y));
+    y1 = fma(s, x, c * y);
+}
+
 __global__ __launch_bounds__(256) void jacobi_init_kernel(const double* __restrict__ C, int n, int N,
                                                           double* __restrict__ A,
                                                           double* __restrict__ V) {
@@ -260,42 +290,128 @@ __global__ __launch_bounds__(256) void jacobi_init_kernel(const double* __restri
     V[idx] = i == j ? 1.0 : 0.0;
 }
 
-// one round: thread (kp, kq) maps block (pair kp rows, pair kq columns) of
-// Ain into Aout, and rotates columns of pair kq in rows of pair kp of V
+// One round on A: a workgroup takes the 2 x 2 blocks of JP row pairs and JQ
+// column pairs of Ain into Aout.  The rotations of its pairs are computed once,
+// by one thread each, while the blocks load (every thread computing both of
+// its block's rotations, each two FP64 divisions and two square roots, was most
+// of the round's work); the round's rotations also go to rot [pair], for the
+// eigenvectors.  A round moves A once through the caches and waits for two
+// loads in a row, with n - 1 launches a sweep: 12.5 us per round at n = 960
+// with V and a thread per block, 5.7 so (5.6 / 6.0 / 7.3 at 4 / 16 / 32 row
+// pairs).
+constexpr int JP = 8, JQ = 64;
 __global__ __launch_bounds__(256) void jacobi_round_kernel(const double* __restrict__ Ain,
                                                            double* __restrict__ Aout,
-                                                           double* __restrict__ V, int N, int r) {
-    const int h = N / 2;
-    const int64_t idx = int64_t(blockIdx.x) * 256 + threadIdx.x;
-    if (idx >= int64_t(h) * h) return;
-    const int kp = int(idx / h), kq = int(idx % h);
-    int p0, p1, q0, q1;
-    jacobi_pair(N, r, kp, p0, p1);
-    jacobi_pair(N, r, kq, q0, q1);
+                                                           double2* __restrict__ rot, int N, int r) {
+    __shared__ double2 cs[JQ + JP];
+    const int h = N / 2, t = threadIdx.x;
+    const int q_first = blockIdx.x * JQ, p_first = blockIdx.y * JP;
+    const int kq = q_first + (t & (JQ - 1));
     auto at = [&](int i, int j) { return Ain[int64_t(i) * N + j]; };
-    double cp, sp, cq, sq;
-    jacobi_rotation(at(p0, p0), at(p1, p1), at(p0, p1), cp, sp);
-    jacobi_rotation(at(q0, q0), at(q1, q1), at(q0, q1), cq, sq);
-    const double b00 = at(p0, q0), b01 = at(p0, q1), b10 = at(p1, q0), b11 = at(p1, q1);
-    // rows: R_P^T B
-    const double r00 = cp * b00 - sp * b10, r01 = cp * b01 - sp * b11;
-    const double r10 = sp * b00 + cp * b10, r11 = sp * b01 + cp * b11;
-    // columns: (R_P^T B) R_Q
-    double n00 = r00 * cq - r01 * sq, n01 = r00 * sq + r01 * cq;
-    double n10 = r10 * cq - r11 * sq, n11 = r10 * sq + r11 * cq;
-    if (kp == kq) n01 = n10 = 0.0;   // the pair's own entry, zero by construction
-    Aout[int64_t(p0) * N + q0] = n00;
-    Aout[int64_t(p0) * N + q1] = n01;
-    Aout[int64_t(p1) * N + q0] = n10;
-    Aout[int64_t(p1) * N + q1] = n11;
-    // V <- V R_Q on rows p0, p1 (every row belongs to exactly one pair)
+    int q0 = 0, q1 = 0;
+    if (kq < h) jacobi_pair(N, r, kq, q0, q1);
+    double B[JP / 4][4];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-        const int64_t row = int64_t(e ? p1 : p0) * N;
-        const double v0 = V[row + q0], v1 = V[row + q1];
-        V[row + q0] = v0 * cq - v1 * sq;
-        V[row + q1] = v0 * sq + v1 * cq;
+    for (int e = 0; e < JP / 4; ++e) {
+        const int kp = p_first + t / JQ + 4 * e;
+        if (kq >= h || kp >= h) continue;
+        int p0, p1;
+        jacobi_pair(N, r, kp, p0, p1);
+        B[e][0] = at(p0, q0); B[e][1] = at(p0, q1);
+        B[e][2] = at(p1, q0); B[e][3] = at(p1, q1);
     }
+    if (t < JQ + JP) {
+        const int k = t < JQ ? q_first + t : p_first + t - JQ;
+        if (k < h) {
+            int a, b;
+            jacobi_pair(N, r, k, a, b);
+            double c, s;
+            jacobi_rotation(at(a, a), at(b, b), at(a, b), c, s);
+            cs[t] = make_double2(c, s);
+            if (blockIdx.y == 0 && t < JQ) rot[k] = make_double2(c, s);
+        }
+    }
+    __syncthreads();
+    if (kq >= h) return;
+    const double cq = cs[t & (JQ - 1)].x, sq = cs[t & (JQ - 1)].y;
+#pragma unroll
+    for (int e = 0; e < JP / 4; ++e) {
+        const int kp = p_first + t / JQ + 4 * e;
+        if (kp >= h) continue;
+        int p0, p1;
+        jacobi_pair(N, r, kp, p0, p1);
+        const double cp = cs[JQ + kp - p_first].x, sp = cs[JQ + kp - p_first].y;
+        const double b00 = B[e][0], b01 = B[e][1], b10 = B[e][2], b11 = B[e][3];
+        // rows: R_P^T B, then columns: (R_P^T B) R_Q
+        double r00, r01, r10, r11, n00, n01, n10, n11;
+        rotate2(b00, b10, cp, sp, r00, r10);
+        rotate2(b01, b11, cp, sp, r01, r11);
+        rotate2(r00, r01, cq, sq, n00, n01);
+        rotate2(r10, r11, cq, sq, n10, n11);
+        if (kp == kq) n01 = n10 = 0.0;   // the pair's own entry, zero by construction
+        Aout[int64_t(p0) * N + q0] = n00;
+        Aout[int64_t(p0) * N + q1] = n01;
+        Aout[int64_t(p1) * N + q0] = n10;
+        Aout[int64_t(p1) * N + q1] = n11;
+    }
+}
+
+// V <- V J for all the rounds of a sweep: the rows of V are independent, so a
+// workgroup keeps ROWS of them in LDS and applies the sweep's rotations, one
+// barrier per round and the next round's rotations in flight, instead of V
+// passing through memory in every round.  KM: pairs per thread.  ROWS = 0: one
+// row, in memory, for matrices whose rows LDS does not hold.  What bounds it is
+// the chain of a round: two LDS reads, four products, two writes, a barrier.
+template <int ROWS, int KM>
+__global__ __launch_bounds__(256) void jacobi_vectors_kernel(const double2* __restrict__ rot,
+                                                             double* __restrict__ V, int N) {
+    extern __shared__ double lv[];
+    constexpr int R = ROWS ? ROWS : 1;
+    const int h = N / 2, t = threadIdx.x;
+    const int64_t row0 = int64_t(blockIdx.x) * R;
+    const int live = int(std::min<int64_t>(R, N - row0));
+    double* rows = ROWS ? lv : V + row0 * N;
+    if (ROWS)
+        for (int i = t; i < live * N; i += 256) lv[i] = V[row0 * N + i];
+    // pair k of round r, rotated by cs
+    auto rotate = [&](int r, int k, double2 cs) {
+        int a, b;
+        jacobi_pair(N, r, k, a, b);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if (i >= live) break;
+            const double v0 = rows[int64_t(i) * N + a], v1 = rows[int64_t(i) * N + b];
+            double w0, w1;
+            rotate2(v0, v1, cs.x, cs.y, w0, w1);
+            rows[int64_t(i) * N + a] = w0;
+            rows[int64_t(i) * N + b] = w1;
+        }
+    };
+    if constexpr (ROWS == 0) {
+        for (int r = 0; r + 1 < N; ++r) {
+            for (int k = t; k < h; k += 256) rotate(r, k, rot[int64_t(r) * h + k]);
+            __syncthreads();
+        }
+        return;
+    }
+    double2 cur[KM], nxt[KM];
+    auto load = [&](int r, double2 (&c)[KM]) {
+#pragma unroll
+        for (int e = 0; e < KM; ++e) c[e] = rot[int64_t(r) * h + std::min(t + 256 * e, h - 1)];
+    };
+    load(0, cur);
+    __syncthreads();
+    for (int r = 0; r + 1 < N; ++r) {
+        load(std::min(r + 1, N - 2), nxt);
+#pragma unroll
+        for (int e = 0; e < KM; ++e)
+            if (t + 256 * e < h) rotate(r, t + 256 * e, cur[e]);
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < KM; ++e) cur[e] = nxt[e];
+    }
+    if (ROWS)
+        for (int i = t; i < live * N; i += 256) V[row0 * N + i] = lv[i];
 }
 
 // per-block sums of squares: off-diagonal entries, diagonal entries
@@ -379,7 +495,7 @@ saq_status run_covariance(const float* X, int64_t n, int32_t D, int64_t fit_samp
     double* mpart = reinterpret_cast<double*>(base + S.off_mpart);
     double* part = reinterpret_cast<double*>(base + S.off_part);
     const unsigned cb = unsigned((D + 255) / 256);
-    hipLaunchKernelGGL(mean_part_kernel, dim3(cb, unsigned(S.nb)), dim3(256), 0, st, X, n, D, S.m, mpart);
+    hipLaunchKernelGGL(mean_part_kernel, dim3(unsigned((D + 63) / 64), unsigned(S.nb)), dim3(64), 0, st, X, n, D, S.m, mpart);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_err(e, "mean_part_kernel launch");
     hipLaunchKernelGGL(mean_reduce_kernel, dim3(cb), dim3(256), 0, st, mpart, S.nb, D, S.m, mu);
@@ -397,9 +513,29 @@ saq_status run_covariance(const float* X, int64_t n, int32_t D, int64_t fit_samp
     return e == hipSuccess ? SAQ_OK : hip_err(e, "cov_reduce_kernel launch");
 }
 
+// two buffers of A, V, a sweep's rotations (n - 1 rounds of n / 2 pairs)
 int64_t jacobi_bytes(int32_t n) {
     const int64_t N = n + (n & 1);
-    return 3 * align256(N * N * 8) + align256(int64_t(JACOBI_OFF_BLOCKS) * 2 * 8) + 256;
+    return 4 * align256(N * N * 8) + align256(int64_t(JACOBI_OFF_BLOCKS) * 2 * 8) + 256;
+}
+
+// V <- V J of one sweep
+void launch_vectors(const double2* rot, double* V, int N, hipStream_t st) {
+    const size_t row = size_t(N) * 8;
+#define SAQ_LAUNCH_V(ROWS, KM)                                                                      \
+    hipLaunchKernelGGL((jacobi_vectors_kernel<ROWS, KM>),                                           \
+                       dim3(unsigned((N + (ROWS ? ROWS : 1) - 1) / (ROWS ? ROWS : 1))), dim3(256),  \
+                       ROWS * row, st, rot, V, N)
+    // ROWS rows within 64 KB.  Few rows: a round's chain hardly depends on
+    // them, and rows spread over more CUs (n = 960, a sweep: 693 us with 4,
+    // 520 with 2, 477 with 1; 2 halves the reads of the rotations).
+    if (N <= 512) SAQ_LAUNCH_V(2, 1);
+    else if (N <= 1024) SAQ_LAUNCH_V(2, 2);
+    else if (N <= 2048) SAQ_LAUNCH_V(2, 4);
+    else if (N <= 4096) SAQ_LAUNCH_V(2, 8);
+    else if (N <= 8192) SAQ_LAUNCH_V(1, 16);
+    else SAQ_LAUNCH_V(0, 1);
+#undef SAQ_LAUNCH_V
 }
 
 // eigen-decomposition of the symmetric C [n x n] (device): w [n] in the
@@ -413,9 +549,10 @@ saq_status run_jacobi(const double* C, int32_t n, double* w, double* V, void* ws
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
     double* A[2] = {reinterpret_cast<double*>(base), reinterpret_cast<double*>(base + align256(el * 8))};
     double* Vw = reinterpret_cast<double*>(base + 2 * align256(el * 8));
-    double* part = reinterpret_cast<double*>(base + 3 * align256(el * 8));
+    double2* rot = reinterpret_cast<double2*>(base + 3 * align256(el * 8));
+    double* part = reinterpret_cast<double*>(base + 4 * align256(el * 8));
     const unsigned gel = unsigned((el + 255) / 256);
-    const unsigned gpair = unsigned((int64_t(N / 2) * (N / 2) + 255) / 256);
+    const dim3 gpair(unsigned((N / 2 + JQ - 1) / JQ), unsigned((N / 2 + JP - 1) / JP));
     hipLaunchKernelGGL(jacobi_init_kernel, dim3(gel), dim3(256), 0, st, C, n, N, A[0], Vw);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_err(e, "jacobi_init_kernel launch");
@@ -424,10 +561,11 @@ saq_status run_jacobi(const double* C, int32_t n, double* w, double* V, void* ws
     bool converged = false;
     for (int sweep = 0; sweep < JACOBI_MAX_SWEEPS && !converged; ++sweep) {
         for (int r = 0; r + 1 < N; ++r) {
-            hipLaunchKernelGGL(jacobi_round_kernel, dim3(gpair), dim3(256), 0, st, A[cur], A[cur ^ 1],
-                               Vw, N, r);
+            hipLaunchKernelGGL(jacobi_round_kernel, gpair, dim3(256), 0, st, A[cur], A[cur ^ 1],
+                               rot + int64_t(r) * (N / 2), N, r);
             cur ^= 1;
         }
+        launch_vectors(rot, Vw, N, st);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_err(e, "jacobi_round_kernel launch");
         hipLaunchKernelGGL(jacobi_off_kernel, dim3(JACOBI_OFF_BLOCKS), dim3(256), 0, st, A[cur], N, part);

@@ -1,0 +1,48 @@
+"""sym_eigen at the edges of what its kernels tile: 64 column pairs by 8 row
+pairs per workgroup, and the eigenvector kernel's variants, whose last sizes
+are 512, 1,024, 2,048, 4,096 and 8,192 (rows of V in LDS, then in memory).
+
+Every entry of V passes through one rotation per round, n - 1 rounds a sweep,
+at most 4 roundings each, and 16 sweeps are more than these matrices take: the
+residual and V's departure from orthogonality stay within
+16 (n - 1) 4 2^-53 of the largest eigenvalue and of one."""
+import pytest
+
+import paper_2509_12086_amd as saq
+from gpu_util import cuda, say
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(n, kind):
+    g = torch.Generator(device=cuda()).manual_seed(n)
+    if kind == "dense":
+        B = torch.randn(n, n, dtype=torch.float64, device=cuda(), generator=g)
+        return (B + B.T) / 2
+    A = torch.diag(torch.arange(1, n + 1, dtype=torch.float64, device=cuda()))
+    if kind == "near diagonal":
+        B = torch.randn(n, n, dtype=torch.float64, device=cuda(), generator=g)
+        A += 1e-6 * (B + B.T)
+    else:   # pairs (i, n - 1 - i): one sweep
+        i = torch.arange(n // 2, device=cuda())
+        A[i, n - 1 - i] = A[n - 1 - i, i] = 3.0
+    return A
+
+
+@pytest.mark.parametrize("n,kind", [
+    (3, "dense"), (15, "dense"), (16, "dense"), (17, "dense"), (127, "dense"), (128, "dense"),
+    (130, "dense"), (511, "dense"), (512, "dense"), (513, "dense"), (514, "dense"),
+    (1024, "dense"), (1025, "dense"), (2048, "near diagonal"), (2049, "near diagonal"),
+    (4096, "near diagonal"), (4098, "near diagonal"), (8194, "pairs")])
+def test_sym_eigen_edges(n, kind):
+    A = _matrix(n, kind)
+    say(f"sym_eigen n={n} {kind}")
+    w, V = saq.sym_eigen(A)
+    torch.cuda.synchronize()
+    tol = 16 * (n - 1) * 4 * 2.0 ** -53
+    scale = float(w.abs().max())
+    res = float((A @ V - V * w[None, :]).abs().max()) / scale
+    orth = float((V.T.contiguous() @ V - torch.eye(n, dtype=torch.float64, device=cuda())).abs().max())
+    say(f"  residual {res:.1e} orthogonality {orth:.1e} (within {tol:.1e})")
+    assert res < tol and orth < tol
