@@ -65,11 +65,18 @@ template <int BI> constexpr int gemm_rows() { return 64 * BI; }
 // so the FP32 rounding error grows with the tile length (32) rather than
 // with D.
 //
-// Tile (64 BI) x 128, k-step 16, four waves of (32 BI) x 64 (BI x 2 blocks of
-// 32 x 32); BI = 2 for FP32 accumulation, 1 for FP64 totals and in grouped
-// launches that also carry FP64-total datasets.  Every output element sees
-// the same MFMA sequence over k in both shapes, so they give identical
-// results.
+// Tile (64 BI) x (64 BJ), k-step 16, four waves of (32 BI) x (32 BJ) (BI x BJ
+// blocks of 32 x 32); BJ = 2, with BI = 2 for FP32 accumulation, 1 for FP64
+// totals and in grouped launches that also carry FP64-total datasets; 64 x 64
+// where a launch has few tiles (small_tiles): what bounds it there is the chain
+// of a k-step, 0.75 us with one workgroup on a CU, and smaller tiles put two or
+// more on each.  Every output element sees the same MFMA sequence over k in
+// all shapes, so they give identical results.
+//
+// With FP64 totals on 64 x 128 the LDS bounds large launches: a step's reads
+// and writes take 420 cycles of a CU's 128 bytes each, its products 384 of a
+// SIMD.  (A 128 x 128 tile, whose totals leave room for one wave per SIMD, takes
+// 10 to 30 % longer.)
 //
 // Per buffer, LDS holds both operands as 16-byte chunks [A|B][term][k half]
 // [row]: a lane's MFMA operand (8 bf16 of one row, k half = lane / 32) is one
@@ -89,11 +96,11 @@ template <int BI> constexpr int gemm_rows() { return 64 * BI; }
 // compute unit (two with per-row references, whose extra c registers would
 // spill at three); FP64 totals run two.
 // ---------------------------------------------------------------------------
-template <int BI> constexpr int split_lds_floats() { return 2 * (6 * 64 * BI + SCB) * 4; }
+template <int BI, int BJ = 2> constexpr int split_lds_floats() { return 2 * 6 * 64 * (BI + BJ) * 4; }
 
 // lds: split_lds_floats<BI>() floats, free on entry; on return free except
 // after a NORM tile (the norm hand-off leaves a barrier-protected write).
-template <int LAYOUT, bool NORM, int BI, bool FULLB, bool REF, bool ACC64>
+template <int LAYOUT, bool NORM, int BI, int BJ, bool FULLB, bool REF, bool ACC64>
 __device__ __forceinline__ void gemm_split_tile_impl(
     bool vec, const float* __restrict__ X, int64_t n, int D, const u32x4* __restrict__ Ms,
     int k_pad, const float* __restrict__ cp, int dk, float* __restrict__ O, int64_t ld,
@@ -101,25 +108,43 @@ __device__ __forceinline__ void gemm_split_tile_impl(
     static_assert(BI == 1 || BI == 2, "tile shapes: 64 x 128 or 128 x 128");
     constexpr int RM = 64 * BI;                 // vectors per tile
     constexpr int SCA = 6 * RM;                 // A chunks per buffer
-    constexpr int SCH = SCA + SCB;              // chunks per buffer
+    constexpr int CN = 64 * BJ;                 // kept dims per tile
+    constexpr int SCH = SCA + 6 * CN;           // chunks per buffer
     u32x4* L = reinterpret_cast<u32x4*>(lds);
     const int64_t m0 = int64_t(tile_m) * RM;
-    const int n0 = tile_n * TN;
+    const int n0 = tile_n * CN;
     const int ksteps = k_pad / SK;
 
     const int t = threadIdx.x;
-    const bool stager = t < 2 * RM;     // threads that stage A
-    const int lr = t % RM;              // A row staged by this thread
-    // its k half of the step, the same for the whole wave: the plan's c is
-    // read with scalar loads
+    // thread t stages XS values of A row t % RM in k half kh of the step (the
+    // same for the whole wave).  With EVEN every thread stages, four of the
+    // half's eight values (the norm's chain needs all eight, XL), and c comes
+    // with them: behind a branch on the thread the compiler cannot count the
+    // loads in flight and waits for all of them in every step, and a scalar
+    // load of c waits for its answer in the middle of one.  Larger tiles and
+    // those with per-row references gain nothing from it (their LDS reads and
+    // loads bound them).
+    constexpr bool EVEN = BJ == 1 && !REF;
+    constexpr int XS = EVEN ? 4 : 8, XL = NORM ? 8 : XS;
+    const int lr = t % RM;
     const int kh = __builtin_amdgcn_readfirstlane((t / RM) & 1);
+    const int h4 = __builtin_amdgcn_readfirstlane(EVEN ? t >> 7 : 0);
+    const int k8 = 8 * kh + (XL == 8 ? 0 : 4 * h4);
+    constexpr bool IN_STAGE = REF || EVEN;  // c is loaded beside X
+    const bool stager = EVEN || t < 2 * RM;
     const int64_t arow = m0 + lr;
     const bool arow_ok = arow < n;
     // rows past n read row n-1 (always valid memory); their outputs and
     // norms are never stored
     const float* xrow = X + (arow_ok ? arow : n - 1) * int64_t(D);
-    // this thread copies B chunks t, t + 256, t + 512 of every k-step
-    const u32x4* msrc = Ms + int64_t(tile_n) * ksteps * SCB + t;
+    // this thread copies B chunks t + 256 p of every k-step; a tile of 64 kept
+    // dims takes its half of each 128 chunks, 384 of them, the last 128 by two
+    // threads each
+    static_assert(SCB == 6 * TN && (BJ == 2 || BI == 1), "B chunks per k-step");
+    constexpr int PB = BJ == 2 ? 3 : 2;
+    const u32x4* msrc = Ms + int64_t(n0 / TN) * ksteps * SCB + (BJ == 2 ? t : 2 * t - (t & 63) + n0 % TN);
+    auto chunk = [&](int p) { return BJ == 2 ? 256 * p : p == 0 ? 0 : t < 128 ? 512 : 256; };
+    const int bdst = BJ == 2 ? 256 : t < 128 ? 256 : 128;
     const float* crow = cp;
     // the plan's c as constant memory: scalar loads also when the pointer
     // comes from a grouped launch's argument struct
@@ -134,44 +159,42 @@ __device__ __forceinline__ void gemm_split_tile_impl(
     double nacc = 0.0;
 
     // raw global values, loaded two k-steps ahead into alternating register
-    // sets: X (and, with per-row references, c) and the B chunks
-    struct Stage { float x[8]; float c[8]; u32x4 b[3]; };
+    // sets: X (and, where IN_STAGE, c) and the B chunks
+    struct Stage { float x[XL]; float c[XL]; u32x4 b[PB]; };
     Stage sA, sB;
     const int kfull = vec ? (D / SK) : 0;
     auto load_stage = [&](int kt, Stage& g, auto fast) {
-        if (stager) {
-            const int kb = kt * SK + 8 * kh;
-            if (decltype(fast)::value || kt < kfull) {
+        const int kb = kt * SK + k8;
+        if (stager && (decltype(fast)::value || kt < kfull)) {
 #pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const float4 x4 = *reinterpret_cast<const float4*>(xrow + kb + 4 * q);
-                    g.x[4 * q + 0] = x4.x; g.x[4 * q + 1] = x4.y; g.x[4 * q + 2] = x4.z; g.x[4 * q + 3] = x4.w;
-                    if (REF) {
-                        const float4 c4 = *reinterpret_cast<const float4*>(crow + kb + 4 * q);
-                        g.c[4 * q + 0] = c4.x; g.c[4 * q + 1] = c4.y;
-                        g.c[4 * q + 2] = c4.z; g.c[4 * q + 3] = c4.w;
-                    }
+            for (int q = 0; q < XL / 4; ++q) {
+                const float4 x4 = *reinterpret_cast<const float4*>(xrow + kb + 4 * q);
+                g.x[4 * q + 0] = x4.x; g.x[4 * q + 1] = x4.y; g.x[4 * q + 2] = x4.z; g.x[4 * q + 3] = x4.w;
+                if (IN_STAGE) {
+                    const float4 c4 = *reinterpret_cast<const float4*>(crow + kb + 4 * q);
+                    g.c[4 * q + 0] = c4.x; g.c[4 * q + 1] = c4.y;
+                    g.c[4 * q + 2] = c4.z; g.c[4 * q + 3] = c4.w;
                 }
-            } else {
+            }
+        } else if (stager) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    g.x[e] = (kb + e < D) ? xrow[kb + e] : 0.f;
-                    if (REF) g.c[e] = (kb + e < D) ? crow[kb + e] : 0.f;
-                }
+            for (int e = 0; e < XL; ++e) {
+                g.x[e] = (kb + e < D) ? xrow[kb + e] : 0.f;
+                // the plan's c is zero padded to k_pad
+                if (IN_STAGE) g.c[e] = (!REF || kb + e < D) ? crow[kb + e] : 0.f;
             }
         }
 #pragma unroll
-        for (int p = 0; p < 3; ++p) g.b[p] = msrc[int64_t(kt) * SCB + 256 * p];
+        for (int p = 0; p < PB; ++p) g.b[p] = msrc[int64_t(kt) * SCB + chunk(p)];
     };
     auto store_step = [&](int kt, int buf, const Stage& g) {
         if (stager) {
-            const int kb = kt * SK + 8 * kh;
-            float ra[8];
+            const int kb = kt * SK + k8;
+            float ra[XL];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                // the plan's c is zero padded to k_pad: one uniform address,
-                // read as constant memory (scalar loads)
-                const float c = REF ? g.c[e] : ccp[kb + e];
+            for (int e = 0; e < XL; ++e) {
+                // one uniform address, read as constant memory (scalar loads)
+                const float c = IN_STAGE ? g.c[e] : ccp[kb + e];
                 ra[e] = g.x[e] - c;
                 if (NORM) {
                     // exact (x - c)^2 in FP64; padding entries are 0 - 0
@@ -179,48 +202,61 @@ __device__ __forceinline__ void gemm_split_tile_impl(
                     nacc = fma(d, d, nacc);
                 }
             }
-            uint32_t a0[4], a1[4], a2[4];
+            if (XL > XS && h4) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) split3(ra[2 * q], ra[2 * q + 1], a0[q], a1[q], a2[q]);
+                for (int e = 0; e < XS; ++e) ra[e] = ra[XL - XS + e];
+            }
+            uint32_t a0[XS / 2], a1[XS / 2], a2[XS / 2];
+#pragma unroll
+            for (int q = 0; q < XS / 2; ++q) split3(ra[2 * q], ra[2 * q + 1], a0[q], a1[q], a2[q]);
             u32x4* A = L + buf * SCH + kh * RM + lr;
-            A[0] = u32x4{a0[0], a0[1], a0[2], a0[3]};
-            A[2 * RM] = u32x4{a1[0], a1[1], a1[2], a1[3]};
-            A[4 * RM] = u32x4{a2[0], a2[1], a2[2], a2[3]};
+            if constexpr (XS == 8) {
+                A[0] = u32x4{a0[0], a0[1], a0[2], a0[3]};
+                A[2 * RM] = u32x4{a1[0], a1[1], a1[2], a1[3]};
+                A[4 * RM] = u32x4{a2[0], a2[1], a2[2], a2[3]};
+            } else {
+                u32x2* A2 = reinterpret_cast<u32x2*>(A) + h4;
+                A2[0] = u32x2{a0[0], a0[1]};
+                A2[4 * RM] = u32x2{a1[0], a1[1]};
+                A2[8 * RM] = u32x2{a2[0], a2[1]};
+            }
         }
         u32x4* B = L + buf * SCH + SCA + t;
 #pragma unroll
-        for (int p = 0; p < 3; ++p) B[256 * p] = g.b[p];
+        for (int p = 0; p < PB; ++p)
+            B[bdst * p] = g.b[p];
     };
 
     const int wave = t >> 6, lane = t & 63;
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, lh = lane >> 5;
-    floatx16 acc[BI][2];
-    double tot[BI][2][ACC64 ? 16 : 1];
+    floatx16 acc[BI][BJ];
+    double tot[BI][BJ][ACC64 ? 16 : 1];
 #pragma unroll
     for (int i = 0; i < BI; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < BJ; ++j) {
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 #pragma unroll
             for (int r = 0; r < (ACC64 ? 16 : 1); ++r) tot[i][j][r] = 0.0;
         }
 
-    // fast: steps kt + 1 and kt + 2 exist and are full (16-byte X loads)
-    auto kstep = [&](int kt, const Stage& cur, Stage& nxt, auto fast) {
+    // fast: steps kt + 1 and kt + 2 exist and are full (16-byte X loads);
+    // par: kt % 2
+    auto kstep = [&](int kt, const Stage& cur, Stage& nxt, auto fast, auto par) {
         constexpr bool F = decltype(fast)::value;
-        const int buf = kt & 1;
+        constexpr int buf = decltype(par)::value;
         if (F || kt + 2 < ksteps) load_stage(kt + 2, nxt, fast);
         const u32x4* Ar = L + buf * SCH + lh * RM + wm * (32 * BI) + li;
-        const u32x4* Br = L + buf * SCH + SCA + lh * TN + wn * 64 + li;
-        u32x4 a[BI][3], b[2][3];
+        const u32x4* Br = L + buf * SCH + SCA + lh * CN + wn * (32 * BJ) + li;
+        u32x4 a[BI][3], b[BJ][3];
 #pragma unroll
         for (int p = 0; p < 3; ++p) {
 #pragma unroll
             for (int i = 0; i < BI; ++i) a[i][p] = Ar[2 * RM * p + 32 * i];
-            b[0][p] = Br[2 * TN * p];
-            if (FULLB) b[1][p] = Br[2 * TN * p + 32];
+            b[0][p] = Br[2 * CN * p];
+            if (FULLB) b[BJ - 1][p] = Br[2 * CN * p + 32];
         }
         // the six products, smallest terms first
         constexpr int TA[6] = {2, 1, 0, 1, 0, 0};
@@ -229,20 +265,20 @@ __device__ __forceinline__ void gemm_split_tile_impl(
         for (int u = 0; u < 6; ++u)
 #pragma unroll
             for (int i = 0; i < BI; ++i) {
-                acc[i][0] = mfma_bf16(a[i][TA[u]], b[0][TB[u]], acc[i][0]);
-                if (FULLB) acc[i][1] = mfma_bf16(a[i][TA[u]], b[1][TB[u]], acc[i][1]);
+                // a k-tile's first product starts from zero
+                const bool from0 = ACC64 && buf == 0 && u == 0;
+                acc[i][0] = mfma_bf16(a[i][TA[u]], b[0][TB[u]], from0 ? floatx16{} : acc[i][0]);
+                if (FULLB)
+                    acc[i][BJ - 1] = mfma_bf16(a[i][TA[u]], b[BJ - 1][TB[u]], from0 ? floatx16{} : acc[i][BJ - 1]);
             }
-        if (ACC64 && (kt & 1)) {
+        if (ACC64 && buf == 1) {
             // end of a 32-wide k-tile: into the FP64 totals
 #pragma unroll
             for (int i = 0; i < BI; ++i)
 #pragma unroll
                 for (int j = 0; j < (FULLB ? 2 : 1); ++j)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        tot[i][j][r & (ACC64 ? 15 : 0)] += double(acc[i][j][r]);
-                        acc[i][j][r] = 0.f;
-                    }
+                    for (int r = 0; r < 16; ++r) tot[i][j][r & (ACC64 ? 15 : 0)] += double(acc[i][j][r]);
         }
         if (F || kt + 1 < ksteps) store_step(kt + 1, buf ^ 1, cur);
         __syncthreads();
@@ -251,34 +287,36 @@ __device__ __forceinline__ void gemm_split_tile_impl(
     store_step(0, 0, sA);
     load_stage(1, sB, std::false_type{});   // k_pad is a multiple of 32: ksteps >= 2, even
     __syncthreads();
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
     // the bulk of the steps with branch-free loads, so the compiler's wait
     // before each store covers only the loads that store needs
     int kt = 0;
     for (; kt + 3 < kfull; kt += 2) {
-        kstep(kt, sB, sA, std::true_type{});
-        kstep(kt + 1, sA, sB, std::true_type{});
+        kstep(kt, sB, sA, std::true_type{}, even);
+        kstep(kt + 1, sA, sB, std::true_type{}, odd);
     }
     for (; kt < ksteps; kt += 2) {
-        kstep(kt, sB, sA, std::false_type{});
-        kstep(kt + 1, sA, sB, std::false_type{});
+        kstep(kt, sB, sA, std::false_type{}, even);
+        kstep(kt + 1, sA, sB, std::false_type{}, odd);
     }
 
     if (NORM) {
         // the row's second half-sum comes from thread t + RM through LDS
         // (free after the last k-step's barrier)
         double* hand = reinterpret_cast<double*>(lds);
-        if (stager && kh == 1) hand[lr] = nacc;
+        if (t < 2 * RM && kh == 1) hand[lr] = nacc;
         __syncthreads();
-        if (stager && kh == 0 && arow_ok)
+        if (t < 2 * RM && kh == 0 && arow_ok)
             norm2[arow] = ref_bad ? __builtin_nanf("") : float(nacc + hand[lr]);
     }
-    // epilogue: lane holds column n0 + wn*64 + 32*bj + li and, for register
+    // epilogue: lane holds column n0 + wn*32*BJ + 32*bj + li and, for register
     // r, row m0 + wm*32*BI + 32*bi + 8*(r/4) + 4*lh + r%4
 #pragma unroll
     for (int bi = 0; bi < BI; ++bi)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj) {
-            const int col = n0 + wn * 64 + bj * 32 + li;
+        for (int bj = 0; bj < BJ; ++bj) {
+            const int col = n0 + wn * (32 * BJ) + bj * 32 + li;
             if (col >= dk) continue;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -299,37 +337,39 @@ __device__ __forceinline__ void gemm_split_tile_impl(
 
 // One output tile.  ||x - c||^2 is produced by the first column tile only;
 // the k-loop is specialised so the other tiles carry none of its work.
-template <int LAYOUT, bool ACC64, int BI, bool REF = false>
+template <int LAYOUT, bool ACC64, int BI, bool REF = false, int BJ = 2>
 __device__ __forceinline__ void gemm_tile(
     bool vec, const float* __restrict__ X, int64_t n, int D, const u32x4* __restrict__ Ms,
     int k_pad, const float* __restrict__ cp, int dk, float* __restrict__ O, int64_t ld,
     float* __restrict__ norm2, int tile_m, int tile_n, float* __restrict__ lds, RefRows R) {
     // the wave's second 32-column block (wave w covers columns
     // 64 (w % 2) .. 64 (w % 2) + 63 of the tile) holds kept dims
-    const bool fullb = tile_n * TN + 64 * int((threadIdx.x >> 6) & 1) + 32 < dk;
+    const bool fullb = BJ == 2 && tile_n * TN + 64 * int((threadIdx.x >> 6) & 1) + 32 < dk;
     if (norm2 != nullptr && tile_n == 0)
-        gemm_split_tile_impl<LAYOUT, true, BI, true, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
-                                                                 O, ld, norm2, tile_m, tile_n, lds, R);
+        gemm_split_tile_impl<LAYOUT, true, BI, BJ, BJ == 2, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
+                                                                        O, ld, norm2, tile_m, tile_n, lds, R);
     else if (fullb)
-        gemm_split_tile_impl<LAYOUT, false, BI, true, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
-                                                                  O, ld, norm2, tile_m, tile_n, lds, R);
+        gemm_split_tile_impl<LAYOUT, false, BI, BJ, BJ == 2, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
+                                                                         O, ld, norm2, tile_m, tile_n, lds, R);
     else
-        gemm_split_tile_impl<LAYOUT, false, BI, false, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
-                                                                   O, ld, norm2, tile_m, tile_n, lds,
-                                                                   R);
+        gemm_split_tile_impl<LAYOUT, false, BI, BJ, false, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
+                                                                       O, ld, norm2, tile_m, tile_n, lds, R);
 }
 
-// FP32 accumulation runs the 128 x 128 tile, FP64 k-tile totals the 64 x 128
-template <bool ACC64> constexpr int gemm_bi() { return ACC64 ? 1 : 2; }
-template <bool ACC64> constexpr int gemm_lds_size() { return split_lds_floats<gemm_bi<ACC64>()>(); }
+// FP32 accumulation runs the 128 x 128 tile, FP64 k-tile totals the 64 x 128;
+// both the 64 x 64 in small launches (small_tiles)
+template <bool ACC64, bool SMALL = false> constexpr int gemm_bi() { return ACC64 || SMALL ? 1 : 2; }
+template <bool ACC64, bool SMALL = false> constexpr int gemm_lds_size() {
+    return split_lds_floats<gemm_bi<ACC64, SMALL>(), SMALL ? 1 : 2>();
+}
 
-template <bool VEC, int LAYOUT, bool ACC64, bool REF>
-__global__ __launch_bounds__(256, (ACC64 || REF) ? 2 : 3) void project_kernel(
+template <bool VEC, int LAYOUT, bool ACC64, bool REF, bool SMALL>
+__global__ __launch_bounds__(256, SMALL ? 3 : (ACC64 || REF) ? 2 : 3) void project_kernel(
     const float* __restrict__ X, int64_t n, int D, const u32x4* __restrict__ Ms, int k_pad, const float* __restrict__ cp, int dk,
     float* __restrict__ O, int64_t ld, float* __restrict__ norm2, int tiles_m, int tiles_n,
     RefRows R, int halves) {
-    constexpr int BI = gemm_bi<ACC64>();
-    __shared__ __attribute__((aligned(16))) float lds[gemm_lds_size<ACC64>()];
+    constexpr int BI = gemm_bi<ACC64, SMALL>();
+    __shared__ __attribute__((aligned(16))) float lds[gemm_lds_size<ACC64, SMALL>()];
     const int bid = blockIdx.x;
     const int xcd = bid % NXCD, local = bid / NXCD;
     int tile_n, tile_m;
@@ -358,8 +398,8 @@ __global__ __launch_bounds__(256, (ACC64 || REF) ? 2 : 3) void project_kernel(
         }
     }
     if (tile_m >= tiles_m) return;
-    gemm_tile<LAYOUT, ACC64, BI, REF>(VEC, X, n, D, Ms, k_pad, cp, dk, O, ld, norm2, tile_m, tile_n,
-                                      lds, R);
+    gemm_tile<LAYOUT, ACC64, BI, REF, SMALL ? 1 : 2>(VEC, X, n, D, Ms, k_pad, cp, dk, O, ld, norm2, tile_m,
+                                                     tile_n, lds, R);
 }
 
 // ---------------------------------------------------------------------------
@@ -719,10 +759,10 @@ struct GemmSet {
 };
 struct GemmArgs { GemmSet set[BATCH_MAX]; int count; int xcd_order; };
 
-template <bool ACC64>
-__global__ __launch_bounds__(256, ACC64 ? 2 : 3) void grouped_gemm_kernel(const GemmArgs args) {
-    constexpr int BI = gemm_bi<ACC64>();
-    __shared__ __attribute__((aligned(16))) float lds[gemm_lds_size<ACC64>()];
+template <bool ACC64, bool SMALL>
+__global__ __launch_bounds__(256, SMALL ? 3 : ACC64 ? 2 : 3) void grouped_gemm_kernel(const GemmArgs args) {
+    constexpr int BI = gemm_bi<ACC64, SMALL>(), BJ = SMALL ? 1 : 2;
+    __shared__ __attribute__((aligned(16))) float lds[gemm_lds_size<ACC64, SMALL>()];
     const int64_t b = blockIdx.x;
     int d = 0;
     while (d + 1 < args.count && b >= args.set[d + 1].first_block) ++d;
@@ -744,11 +784,11 @@ __global__ __launch_bounds__(256, ACC64 ? 2 : 3) void grouped_gemm_kernel(const 
     // one tile shape per launch: in a launch with FP64 totals, datasets
     // without them accumulate in FP32 on the same tile
     if (S.acc64)
-        gemm_tile<LAYOUT_TILES, ACC64, BI>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad, S.cp, S.dk,
+        gemm_tile<LAYOUT_TILES, ACC64, BI, false, BJ>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad, S.cp, S.dk,
                                           S.O, S.ld, S.norm2, tile_m, tile_n, lds,
                                           RefRows{nullptr, nullptr, 0});
     else
-        gemm_tile<LAYOUT_TILES, false, BI>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad, S.cp, S.dk,
+        gemm_tile<LAYOUT_TILES, false, BI, false, BJ>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad, S.cp, S.dk,
                                           S.O, S.ld, S.norm2, tile_m, tile_n, lds,
                                           RefRows{nullptr, nullptr, 0});
 }
@@ -1757,6 +1797,28 @@ const float* dev_S(const saq_plan* p) {
 
 int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
+// 64 x 64 projection tiles where a launch has few of the larger ones, `tiles`
+// of 128 x 128, or of 64 x 128 when some rows take FP64 totals (any64): up to
+// the number that gives most of the 256 CUs one or two.  Project time with the
+// larger and with the small tiles, us (rows x dims, tiles):
+//   FP32     2000 x 768, 64: 46, 28    6000 x 768, 188: 50, 42    8000 x 768, 252: 53, 55
+//            1000 x 960, 56: 61, 33    3000 x 960, 168: 65, 52    4000 x 960, 224: 69, 67
+//   totals   1250 x 768, 100: 38, 27   4000 x 768, 315: 50, 43    5000 x 768, 395: 52, 56
+//            1000 x 1536, 160: 75, 54  2000 x 1536, 320: 90, 82   3000 x 1536, 470: 101, 115
+//   references per row (two loads per row and step, their cost doubled)
+//            1000 x 960, 56: 52, 37    2000 x 960, 112: 55, 45    4000 x 960, 224: 61, 87
+//            1200 x 1536, 190: 68, 75
+// Rows without 16-byte loads stay with the larger tiles (2000 x 333: 25, 27).
+bool small_tiles(int64_t tiles, bool any64, bool vec, bool ref) {
+    return vec && tiles < (ref ? 128 : any64 ? 360 : 224);
+}
+int64_t large_tiles(const saq_plan* p, int64_t n, int bi) {
+    return (n + 64 * bi - 1) / (64 * bi) * (p->layout.n_pad / TN);
+}
+int column_tiles(const saq_plan* p, bool small) {
+    return small ? std::max(1, (p->D_kept + 63) / 64) : p->layout.n_pad / TN;
+}
+
 saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O, int64_t ld,
                           int layout, float* norm2, hipStream_t st,
                           RefRows R = RefRows{nullptr, nullptr, 0}, bool fill = true) {
@@ -1770,12 +1832,16 @@ saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O
                                 p->layout.k_pad, p->D_kept, R.K, p->acc64,
                                 fill && layout == LAYOUT_TILES};
     if (saq::few_rows(&item, 1)) return saq::launch_project_few(&item, 1, layout, st);
-    const int rows = p->acc64 ? gemm_rows<gemm_bi<true>()>() : gemm_rows<gemm_bi<false>()>();
+    const bool ref = R.refs != nullptr;
+    const bool vec = (p->D % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0) &&
+                     ((reinterpret_cast<uintptr_t>(R.refs) & 15) == 0);
+    const bool small = small_tiles(large_tiles(p, n, p->acc64 ? 1 : 2), p->acc64, vec, ref);
+    const int rows = p->acc64 || small ? gemm_rows<1>() : gemm_rows<2>();
     const int tiles_m = int((n + rows - 1) / rows);
-    const int tiles_n = p->layout.n_pad / TN;
+    const int tiles_n = column_tiles(p, small);
     // two halves of the XCDs when the pre-split M is larger than one L2 (4 MB)
     // and half of it fits
-    const int64_t ms_bytes = int64_t(tiles_n) * (p->layout.k_pad / SK) * SCB * 16;
+    const int64_t ms_bytes = int64_t(p->layout.n_pad / TN) * (p->layout.k_pad / SK) * SCB * 16;
     const int halves = (tiles_n >= 2 && ms_bytes > (int64_t(4) << 20) && ms_bytes <= (int64_t(7) << 20)) ? 1 : 0;
     int64_t slots;
     if (!halves) {
@@ -1787,16 +1853,15 @@ saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O
         slots = rows * std::max(cm, tiles_n - cm - odd) + (odd ? rows_mid : 0);
     }
     const dim3 grid(unsigned(NXCD * slots));
-    const bool vec = (p->D % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0) &&
-                     ((reinterpret_cast<uintptr_t>(R.refs) & 15) == 0);
-#define SAQ_LAUNCH_PROJ(V, L, A, F)                                                               \
-    hipLaunchKernelGGL((project_kernel<V, L, A, F>), grid, dim3(256), 0, st, X, n, p->D, dev_Ms(p),\
+#define SAQ_LAUNCH_PROJ1(V, L, A, F, S)                                                           \
+    hipLaunchKernelGGL((project_kernel<V, L, A, F, S>), grid, dim3(256), 0, st, X, n, p->D, dev_Ms(p),\
                        p->layout.k_pad, dev_c(p), p->D_kept, O, ld, norm2, tiles_m, tiles_n, R,  \
                        halves)
+#define SAQ_LAUNCH_PROJ(V, L, A, F) \
+    do { if (small) SAQ_LAUNCH_PROJ1(V, L, A, F, true); else SAQ_LAUNCH_PROJ1(V, L, A, F, false); } while (0)
 #define SAQ_LAUNCH_PROJ2(V, L, F) \
     do { if (p->acc64) SAQ_LAUNCH_PROJ(V, L, true, F); else SAQ_LAUNCH_PROJ(V, L, false, F); } while (0)
     // references per row exist for the tiled (encode) and row (query) layouts
-    const bool ref = R.refs != nullptr;
     if (layout == LAYOUT_TILES) {
         if (ref) {
             if (vec) SAQ_LAUNCH_PROJ2(true, LAYOUT_TILES, true); else SAQ_LAUNCH_PROJ2(false, LAYOUT_TILES, true);
@@ -1814,6 +1879,7 @@ saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O
     }
 #undef SAQ_LAUNCH_PROJ2
 #undef SAQ_LAUNCH_PROJ
+#undef SAQ_LAUNCH_PROJ1
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SAQ_OK : hip_fail(e, "project_kernel launch");
 }
@@ -1877,6 +1943,7 @@ struct BatchPlan {
     int bi = 2;               // projection tile rows / 64
     bool fused = true;
     bool wide = false;
+    bool small = false;       // grouped: 64 x 64 projection tiles
     bool any64 = false;       // some dataset takes FP64 k-tile totals
     size_t lds = 0;           // grouped: quantize LDS; fused: the kernel's dynamic LDS
 };
@@ -1951,7 +2018,17 @@ saq_status plan_batch(const saq_batch_item* items, int32_t count, int32_t rounds
     B.q.rounds = B.f.rounds = rounds;
     B.q.wmax = B.f.wmax = wmax;
     B.f.items = 0;
-    const int rows = 64 * B.bi;
+    if (!B.fused && rows_req == 0) {
+        int64_t tiles = 0;
+        bool vec = true;
+        for (int i = 0; i < count; ++i) {
+            tiles += large_tiles(items[i].plan, items[i].n, B.bi);
+            vec = vec && (items[i].n == 0 || (items[i].plan->D % 4 == 0 &&
+                                              (reinterpret_cast<uintptr_t>(items[i].X_dev) & 15) == 0));
+        }
+        B.small = small_tiles(tiles, B.any64, vec, false);
+    }
+    const int rows = B.small ? 64 : 64 * B.bi;
     for (int i = 0; i < count; ++i) {
         const saq_batch_item& it = items[i];
         if (it.n == 0) continue;
@@ -1962,7 +2039,7 @@ saq_status plan_batch(const saq_batch_item* items, int32_t count, int32_t rounds
         const int vec = (p->D % 4 == 0) && ((reinterpret_cast<uintptr_t>(it.X_dev) & 15) == 0);
         const uintptr_t cb = reinterpret_cast<uintptr_t>(it.codes_dev);
         const int codes_align = (cb & 3) == 0 ? 4 : (cb & 1) == 0 ? 2 : 1;
-        const int tiles_m = int((it.n + rows - 1) / rows), tiles_n = p->layout.n_pad / TN;
+        const int tiles_m = int((it.n + rows - 1) / rows), tiles_n = column_tiles(p, B.small);
         GemmSet& G = B.g.set[B.g.count++];
         G.X = it.X_dev; G.n = it.n; G.D = p->D; G.acc64 = p->acc64 ? 1 : 0; G.vec = vec;
         G.Ms = dev_Ms(p); G.k_pad = p->layout.k_pad; G.cp = dev_c(p); G.dk = p->D_kept;
@@ -2242,10 +2319,13 @@ saq_status saq_encode_batched(const saq_batch_item* items, int32_t count, int32_
     // with FP64 k-tile totals, the 128-row one keeps three workgroups per CU
     if (B.few_rows) {
         if (saq_status s = saq::launch_project_few(B.rows, B.q.count, LAYOUT_TILES, st); s != SAQ_OK) return s;
-    } else if (B.bi == 1)
-        hipLaunchKernelGGL(grouped_gemm_kernel<true>, dim3(unsigned(B.gemm_blocks)), dim3(256), 0, st, B.g);
-    else
-        hipLaunchKernelGGL(grouped_gemm_kernel<false>, dim3(unsigned(B.gemm_blocks)), dim3(256), 0, st, B.g);
+    } else {
+        const dim3 gb(static_cast<unsigned>(B.gemm_blocks)), tb(256);
+        if (B.small && B.any64) hipLaunchKernelGGL((grouped_gemm_kernel<true, true>), gb, tb, 0, st, B.g);
+        else if (B.small) hipLaunchKernelGGL((grouped_gemm_kernel<false, true>), gb, tb, 0, st, B.g);
+        else if (B.bi == 1) hipLaunchKernelGGL((grouped_gemm_kernel<true, false>), gb, tb, 0, st, B.g);
+        else hipLaunchKernelGGL((grouped_gemm_kernel<false, false>), gb, tb, 0, st, B.g);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "grouped_gemm_kernel launch");
     if (B.few) return saq::launch_quantize_few(B.item, B.q.count, rounds, st);

@@ -298,20 +298,25 @@ int64_t item_blocks(const ProjectItem& i) {
 
 namespace saq {
 
-// Where the line lies.  project_kernel's time is flat up to about 4,000 rows,
-// about 0.7 us per k-step; this kernel takes 256 workgroups at a time, 6 us a
-// time at D = 128, 11 at 768 and 20 at 3072.  Measured, us there / here: D =
-// 768 (608 kept) 35 / 10 with 1 row, 36 / 13 with 300, 38 / 33 with 1,000, 39
-// / 54 with 2,000; D = 3072 (2,720 kept) 137 / 25 with 1, 135 / 86 with 300,
-// 145 / 218 with 1,000; D = 128 (96 kept) 8.6 / 5.5 with 1, 9.3 / 7.6 with
-// 2,000, 10 / 13 with 4,000.
+// Where the line lies.  project_kernel's time is nearly flat while its 64 x 64
+// tiles fit the chip at once; this kernel takes 512 workgroups at a time (256
+// without FP64 totals, whose chain passes from wave to wave).  Measured, us
+// there / here, at a number of workgroups here: D = 768 with totals (608 kept)
+// 23 / 13 at 200, 26 / 23 at 500, 27 / 33 at 640; D = 1536 51 / 35 at 400, 54 / 54
+// at 760; D = 3072 97 / 95 at 690, 111 / 185 at 1,325; without totals D = 768
+// 23 / 24 at 285, 24 / 27 at 480, 26 / 38 at 705; D = 960 28 / 26 at 280, 33 / 41 at
+// 530, with references 35 / 36 at 450.  Rows without 16-byte loads have only the
+// larger tiles there, 0.7 us per k-step: D = 333 25 / 22 at 350.
 bool few_rows(const ProjectItem* items, int count) {
     double share = 0.0;
     int64_t blocks = 0;
     for (int i = 0; i < count; ++i) {
-        const int64_t b = item_blocks(items[i]);
+        const ProjectItem& it = items[i];
+        const int64_t b = item_blocks(it);
+        const bool vec = it.D % 4 == 0 &&
+                         ((reinterpret_cast<uintptr_t>(it.X) | reinterpret_cast<uintptr_t>(it.refs)) & 15) == 0;
         blocks += b;
-        share += double(b) / (300.0 + 8.0 * (items[i].k_pad / SK));
+        share += double(b) / (!vec ? 300 + 8 * (it.k_pad / SK) : it.acc64 ? 512 : it.refs ? 450 : 300);
     }
     return blocks > 0 && share <= 1.0;
 }
