@@ -350,6 +350,12 @@ __device__ __forceinline__ float join_digits(int s0, int s1, int s2, int s3) {
 // waves share one step's digits through LDS, double buffered; the digits of the
 // step after next are fetched while the next step runs, and a group's codes
 // after them, so that waiting for the digits leaves the codes in flight.
+//
+// 64 queries, 1M records of 768 dims at 4 b/dim: 717 us on split bf16 operands,
+// 490 so; 100 queries, 250,007 records of 3,072 dims at 2 bits: 980 and 440.
+// In the first the VALU is busy 45 % of the time (half of it where passes end),
+// the LDS 43 %, the matrix cores 17 %; two waves per SIMD do not cover each
+// other's waits.  32-query tiles, with three, decode twice: 700 us.
 template <int QB, int NL>
 __global__ __launch_bounds__(256, 2) void scan_kernel(
     const u32x4* __restrict__ Qd, int nq, const float* __restrict__ qn2, const int* __restrict__ qexp,
@@ -529,8 +535,16 @@ __global__ __launch_bounds__(256, 2) void scan_kernel(
 // work where a pass ends), so four workgroups per CU keep the record stream in
 // flight.  Lane: records lane % 16 and 16 + lane % 16 of the wave, dims
 // 16 (lane / 16) .. + 15 of a step; the two records' 16-bit pieces of a plane
-// share a word, are transposed together and parted again.
-template <int NL>
+// share a word, are transposed together and parted again.  FOUR: at most four
+// queries, each the operand's rows 4 q .. 4 q + 3, so that the first of a lane's
+// four sums is query lane / 16's and the others need no work.
+//
+// One query, 1M records of 1,536 dims at 4 b/dim (820 MB): 979 us on split bf16
+// operands, 278 for the whole call so (300 with four sums per lane, whose VALU
+// work is 28 % more).  The VALU is busy 58 % of that time, the texture
+// addresser 46 %; the rest is the chain of a step: LDS reads, transposition,
+// products.
+template <int NL, bool FOUR>
 __global__ __launch_bounds__(256, 3) void scan_few_kernel(
     const u32x4* __restrict__ Qd, int nq, const float* __restrict__ qn2, const int* __restrict__ qexp,
     const float* __restrict__ qh, const Pass* __restrict__ passes, int count, int n_kept,
@@ -545,45 +559,47 @@ __global__ __launch_bounds__(256, 3) void scan_few_kernel(
     const int t = threadIdx.x, lane = t & 63, ri = lane & 15, kg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t rec0 = int64_t(rtile) * TR + wave * WR + ri;      // and rec0 + 16
-    const int low0 = int(min(rec0, n - 1) * code_bytes) & 15, low1 = int(min(rec0 + 16, n - 1) * code_bytes) & 15;
+    constexpr int R = FOUR ? 1 : 4;                                 // sums used per record
+    auto query = [&](int r) { return FOUR ? kg : 4 * kg + r; };
+    // rec0 + 16's bytes start at the same place of a 16-byte unit (past the last
+    // record: somewhere in its row, never stored)
+    const int low = int(min(rec0, n - 1) * code_bytes) & 15;
     const FactorStage fs(flds[wave], factors, n_kept, int64_t(rtile) * TR + wave * WR, n, lane);
     const Stage stage(clds[wave], codes, tail, tail_tile, rtile, code_bytes, n, wave, lane, align_mask);
     const int cl = ri * Stage::ROW + 2 * kg;
 
-    float tot[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    float tot[2][R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) tot[0][r] = tot[1][r] = 0.f;
     if (n_kept > 0) {
         Pass P = passes[0];
         auto c = stage.load(P);
         for (int u = t; u < steps * 4 * ND * nq; u += 256) qres[u] = Qd[u];
         stage.store(c);
         __syncthreads();
-        const u32x4* Abase = qres + kg * nq + min(ri, nq - 1);
+        const u32x4* Abase = qres + kg * nq + min(FOUR ? ri >> 2 : ri, nq - 1);
         int ip = 0;
         while (ip < count) {
             const int next = ip + (P.info >> 16), goff = P.off;
-            const int row0 = cl + stage.first(low0, goff), row1 = cl + 16 * Stage::ROW + stage.first(low1, goff);
+            const int row0 = cl + stage.first(low, goff);
             // the next group's codes (behind the last group the last pass's, unused)
             c = stage.load(passes[min(next, count - 1)]);
             for (; ip < next; ++ip) {
                 const Pass N = passes[min(ip + 1, count - 1)];
-                const int first0 = row0 + (P.off - goff), first1 = row1 + (P.off - goff);
+                const int first = row0 + (P.off - goff);
                 i32x4 acc[ND][2];
-#pragma unroll
-                for (int d = 0; d < ND; ++d) acc[d][0] = acc[d][1] = i32x4{0, 0, 0, 0};
-#pragma unroll 1
-                for (int st = 0; st < P.steps; ++st) {
+                auto step = [&](int st, auto zero) {
                     const u32x4* A = Abase + (P.q0 + st) * 4 * ND * nq;
                     i32x4 a[ND];
 #pragma unroll
                     for (int d = 0; d < ND; ++d) a[d] = __builtin_bit_cast(i32x4, A[d * 4 * nq]);
                     uint32_t w[8];
-                    const unsigned char* ca = clds[wave] + here(first0 + 8 * st);
-                    const unsigned char* cb = clds[wave] + here(first1 + 8 * st);
+                    const unsigned char* src = clds[wave] + here(first + 8 * st);
                     switch (P.b) {
-#define SAQ_DECODE(K) case K: decode_pair<K>(ca, cb, P.pb, w); break;
+#define SAQ_DECODE(K) case K: decode_pair<K>(src, src + 16 * Stage::ROW, P.pb, w); break;
                         SAQ_DECODE(1) SAQ_DECODE(2) SAQ_DECODE(3) SAQ_DECODE(4)
                         SAQ_DECODE(5) SAQ_DECODE(6) SAQ_DECODE(7)
-                        default: decode_pair<8>(ca, cb, P.pb, w); break;
+                        default: decode_pair<8>(src, src + 16 * Stage::ROW, P.pb, w); break;
 #undef SAQ_DECODE
                     }
                     // bytes 0, 1 of w[i]: dims i, 8 + i of the first record, bytes
@@ -596,19 +612,28 @@ __global__ __launch_bounds__(256, 3) void scan_few_kernel(
                     }
 #pragma unroll
                     for (int d = 0; d < ND; ++d) {
+                        if (decltype(zero)::value) acc[d][0] = acc[d][1] = i32x4{0, 0, 0, 0};
                         acc[d][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[d], B0, acc[d][0], 0, 0, 0);
                         acc[d][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[d], B1, acc[d][1], 0, 0, 0);
                     }
-                }
+                };
+                step(0, std::true_type{});
+#pragma unroll 1
+                for (int st = 1; st < P.steps; ++st) step(st, std::false_type{});
                 const float ga = ldexpf(fs.get(ri, P.s), P.wexp), gb = ldexpf(fs.get(ri + 16, P.s), P.wexp);
-                const float4 h = (P.info & 1) ? *reinterpret_cast<const float4*>(qh + P.s * padded_queries(nq) + 4 * kg)
-                                        : make_float4(0.f, 0.f, 0.f, 0.f);
-                const float hv[4] = {h.x, h.y, h.z, h.w};
+                float h[R];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    tot[0][r] = fmaf(ga, join_digits(acc[0][0][r], acc[1][0][r], acc[2][0][r], acc[3][0][r]) + hv[r],
+                for (int r = 0; r < R; ++r) h[r] = 0.f;
+                if (P.info & 1) {
+                    const float* src = qh + P.s * padded_queries(nq) + query(0);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) h[r] = src[r];
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    tot[0][r] = fmaf(ga, join_digits(acc[0][0][r], acc[1][0][r], acc[2][0][r], acc[3][0][r]) + h[r],
                                      tot[0][r]);
-                    tot[1][r] = fmaf(gb, join_digits(acc[0][1][r], acc[1][1][r], acc[2][1][r], acc[3][1][r]) + hv[r],
+                    tot[1][r] = fmaf(gb, join_digits(acc[0][1][r], acc[1][1][r], acc[2][1][r], acc[3][1][r]) + h[r],
                                      tot[1][r]);
                 }
                 P = N;
@@ -616,10 +641,9 @@ __global__ __launch_bounds__(256, 3) void scan_few_kernel(
             stage.store(c);
         }
     }
-    // register r: query 4 kg + r
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int q = 4 * kg + r;
+    for (int r = 0; r < R; ++r) {
+        const int q = query(r);
         if (q >= nq) break;
         const float qn = qn2[q];
         const int e = qexp[q] - (QEXP - 1);
@@ -792,8 +816,8 @@ saq_status scan_impl(const saq_plan* p, const float* Q, int32_t nq, const float*
     hipLaunchKernelGGL((scan_kernel<QB, NL>), grid, dim3(256), 0, st, Qd, nq, qn2, qexp, qh, passes, \
                        int(pv.size()), p->n_kept, steps, codes, p->code_bytes, align_mask, tail,              \
                        int(tail_tile), factors, n, int(rtiles), qtiles, out)
-#define SAQ_LAUNCH_FEW(NL)                                                                           \
-    hipLaunchKernelGGL((scan_few_kernel<NL>), dim3(unsigned(rtiles)), dim3(256), resident, st, Qd,   \
+#define SAQ_LAUNCH_FEW(NL, FOUR)                                                                     \
+    hipLaunchKernelGGL((scan_few_kernel<NL, FOUR>), dim3(unsigned(rtiles)), dim3(256), resident, st, Qd,   \
                        nq, qn2, qexp, qh, passes, int(pv.size()), p->n_kept, steps, codes, p->code_bytes,     \
                        align_mask, tail, int(tail_tile), factors, n, int(rtiles), out)
 #define SAQ_BY_LOADS(LAUNCH)                                                                         \
@@ -801,15 +825,20 @@ saq_status scan_impl(const saq_plan* p, const float* Q, int32_t nq, const float*
         if (nl == MIN_LOADS) LAUNCH(MIN_LOADS);                                                      \
         else LAUNCH(MAXNL);                                                                          \
     } while (0)
+#define SAQ_LAUNCH_FEW4(NL) SAQ_LAUNCH_FEW(NL, true)
+#define SAQ_LAUNCH_FEW16(NL) SAQ_LAUNCH_FEW(NL, false)
 #define SAQ_LAUNCH_SCAN1(NL) SAQ_LAUNCH_SCAN(1, NL)
 #define SAQ_LAUNCH_SCAN2(NL) SAQ_LAUNCH_SCAN(2, NL)
-    if (few) SAQ_BY_LOADS(SAQ_LAUNCH_FEW);
+    if (few && nq <= 4) SAQ_BY_LOADS(SAQ_LAUNCH_FEW4);
+    else if (few) SAQ_BY_LOADS(SAQ_LAUNCH_FEW16);
     else if (tq == TQ / 2) SAQ_BY_LOADS(SAQ_LAUNCH_SCAN1);
     else SAQ_BY_LOADS(SAQ_LAUNCH_SCAN2);
 #undef SAQ_LAUNCH_SCAN
 #undef SAQ_LAUNCH_SCAN1
 #undef SAQ_LAUNCH_SCAN2
 #undef SAQ_LAUNCH_FEW
+#undef SAQ_LAUNCH_FEW4
+#undef SAQ_LAUNCH_FEW16
 #undef SAQ_BY_LOADS
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SAQ_OK : saq::hip_status(e, "scan_kernel launch");

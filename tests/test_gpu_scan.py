@@ -97,3 +97,12 @@ def test_scan_record_counts_and_alignments(n):
 def test_scan_prefixes(prefix):
     for nq in (2, 50):
         _check(*_case([70, 64, 300], [16, 9, 8], 150, nq, prefix), prefix=prefix, label=f"prefix {prefix}")
+
+
+@pytest.mark.parametrize("nq", [1, 3, 4, 5])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 31, 33, 130])
+def test_scan_up_to_four_queries(nq, n):
+    """At most four queries take one sum per lane and record; records 16 apart
+    share their place in a 16-byte unit whatever the record length."""
+    _check(*_case([33, 80, 24], [8, 5, 3], n, nq, nq + n), label="four queries, odd record length")
+    _check(*_case([130, 400], [9, 2], n, nq, nq + n), label="four queries, several runs")
