@@ -280,6 +280,20 @@ __device__ __forceinline__ void rotate2(double x, double y, double c, double s, 
     y1 = fma(s, x, c * y);
 }
 
+// R_P^T B R_Q of the block of a row pair and a column pair, rows first; own: the
+// pair's own block, whose off-diagonal entries are zero by construction
+struct Block { double v[2][2]; };
+__device__ __forceinline__ Block rotate_block(const Block& b, double2 p, double2 q, bool own) {
+    double r00, r01, r10, r11;
+    Block n;
+    rotate2(b.v[0][0], b.v[1][0], p.x, p.y, r00, r10);
+    rotate2(b.v[0][1], b.v[1][1], p.x, p.y, r01, r11);
+    rotate2(r00, r01, q.x, q.y, n.v[0][0], n.v[0][1]);
+    rotate2(r10, r11, q.x, q.y, n.v[1][0], n.v[1][1]);
+    if (own) n.v[0][1] = n.v[1][0] = 0.0;
+    return n;
+}
+
 __global__ __launch_bounds__(256) void jacobi_init_kernel(const double* __restrict__ C, int n, int N,
                                                           double* __restrict__ A,
                                                           double* __restrict__ V) {
@@ -290,7 +304,8 @@ __global__ __launch_bounds__(256) void jacobi_init_kernel(const double* __restri
     V[idx] = i == j ? 1.0 : 0.0;
 }
 
-// One round on A: a workgroup takes the 2 x 2 blocks of JP row pairs and JQ
+// One round on A (the last one of a sweep, jacobi_two_kernel taking the others
+// in twos): a workgroup takes the 2 x 2 blocks of JP row pairs and JQ
 // column pairs of Ain into Aout.  The rotations of its pairs are computed once,
 // by one thread each, while the blocks load (every thread computing both of
 // its block's rotations, each two FP64 divisions and two square roots, was most
@@ -341,18 +356,119 @@ __global__ __launch_bounds__(256) void jacobi_round_kernel(const double* __restr
         int p0, p1;
         jacobi_pair(N, r, kp, p0, p1);
         const double cp = cs[JQ + kp - p_first].x, sp = cs[JQ + kp - p_first].y;
-        const double b00 = B[e][0], b01 = B[e][1], b10 = B[e][2], b11 = B[e][3];
-        // rows: R_P^T B, then columns: (R_P^T B) R_Q
-        double r00, r01, r10, r11, n00, n01, n10, n11;
-        rotate2(b00, b10, cp, sp, r00, r10);
-        rotate2(b01, b11, cp, sp, r01, r11);
-        rotate2(r00, r01, cq, sq, n00, n01);
-        rotate2(r10, r11, cq, sq, n10, n11);
-        if (kp == kq) n01 = n10 = 0.0;   // the pair's own entry, zero by construction
-        Aout[int64_t(p0) * N + q0] = n00;
-        Aout[int64_t(p0) * N + q1] = n01;
-        Aout[int64_t(p1) * N + q0] = n10;
-        Aout[int64_t(p1) * N + q1] = n11;
+        const Block b{{{B[e][0], B[e][1]}, {B[e][2], B[e][3]}}};
+        const Block n = rotate_block(b, make_double2(cp, sp), make_double2(cq, sq), kp == kq);
+        Aout[int64_t(p0) * N + q0] = n.v[0][0];
+        Aout[int64_t(p0) * N + q1] = n.v[0][1];
+        Aout[int64_t(p1) * N + q0] = n.v[1][0];
+        Aout[int64_t(p1) * N + q1] = n.v[1][1];
+    }
+}
+
+// Rounds r and r + 1 on A in one pass over it (r + 2 < N).  A player's partner
+// changes to that of a neighbouring pair, so pair k of round r + 1 is made of
+// players of round r's pairs k - 1 .. k + 1: a workgroup that loads SP x SQ
+// blocks of round r has what it needs for the (SP - 2) x (SQ - 2) inside them in
+// round r + 1.  The rotations of round r + 1 need three entries of A after round
+// r, which one thread per pair works out from the blocks that hold them.  Every
+// entry sees the operations of two single rounds.  What bounds it is the chain of
+// loads, two rotations and barriers: n = 960, two rounds 11.5 us one by one, 7.5
+// so (8.7 with 16 x 32 blocks and 256 threads, 7.7 with 32 x 32 and 1,024).
+constexpr int SP = 32, SQ = 64, IP = SP - 2, IQ = SQ - 2, TWO_T = 1024;
+__global__ __launch_bounds__(TWO_T) void jacobi_two_kernel(const double* __restrict__ Ain,
+                                                           double* __restrict__ Aout,
+                                                           double2* __restrict__ rot, int N, int r) {
+    __shared__ double2 T[2 * SP][SQ + 1];      // A after round r: [2 row slot + side][column slot]
+    __shared__ double2 cs0[SQ + SP];           // rotations of round r: column slots, row slots
+    __shared__ double2 cs1[IQ + IP];           // of round r + 1
+    __shared__ int2 loc[IQ + IP];              // its players as 2 slot + side
+    const int h = N / 2, t = threadIdx.x;
+    const int q_first = int(blockIdx.x) * IQ - 1, p_first = int(blockIdx.y) * IP - 1;   // pairs of slot 0
+    auto at = [&](int i, int j) { return Ain[int64_t(i) * N + j]; };
+    auto load = [&](int kp, int kq) {
+        int p0, p1, q0, q1;
+        jacobi_pair(N, r, kp, p0, p1);
+        jacobi_pair(N, r, kq, q0, q1);
+        return Block{{{at(p0, q0), at(p0, q1)}, {at(p1, q0), at(p1, q1)}}};
+    };
+    auto inside = [&](int k) { return min(max(k, 0), h - 1); };   // slots past the pairs: never used
+    constexpr int BLOCKS = SP * SQ / TWO_T;
+    Block B[BLOCKS];
+#pragma unroll
+    for (int e = 0; e < BLOCKS; ++e)
+        B[e] = load(inside(p_first + t / SQ + TWO_T / SQ * e), inside(q_first + t % SQ));
+    // round r + 1's pairs, threads TWO_T - IQ - IP on: columns, then rows
+    const int nx = t - (TWO_T - IQ - IP);
+    const int first = nx < IQ ? q_first : p_first, k1 = first + 1 + (nx < IQ ? nx : nx - IQ);
+    const bool next = nx >= 0 && k1 < h;
+    Block X{}, Y{}, Z{};
+    int ka = 0, kb = 0, sa = 0, sb = 0;
+    if (next) {
+        // player x in round r: its pair, and its side of it
+        auto player = [&](int x, int& k, int& side) {
+            const int m = N - 1, d = x >= r ? x - r : x - r + m;
+            k = x == m ? 0 : d < h ? d : m - d;
+            int a, b;
+            jacobi_pair(N, r, k, a, b);
+            side = x == b;
+        };
+        int a, b;
+        jacobi_pair(N, r + 1, k1, a, b);
+        player(a, ka, sa);
+        player(b, kb, sb);
+        X = load(ka, ka);
+        Y = load(kb, kb);
+        Z = load(ka, kb);
+        loc[nx] = make_int2(2 * (ka - first) + sa, 2 * (kb - first) + sb);
+    }
+    if (t < SQ + SP) {
+        const int k = t < SQ ? q_first + t : p_first + t - SQ;
+        if (k >= 0 && k < h) {
+            int a, b;
+            jacobi_pair(N, r, k, a, b);
+            double c, s;
+            jacobi_rotation(at(a, a), at(b, b), at(a, b), c, s);
+            cs0[t] = make_double2(c, s);
+            if (blockIdx.y == 0 && t >= 1 && t <= IQ) rot[k] = make_double2(c, s);
+        }
+    }
+    __syncthreads();
+    if (next) {
+        const double2* c0 = cs0 + (nx < IQ ? 0 : SQ) - first;
+        X = rotate_block(X, c0[ka], c0[ka], true);
+        Y = rotate_block(Y, c0[kb], c0[kb], true);
+        Z = rotate_block(Z, c0[ka], c0[kb], false);
+        auto side = [](const Block& b, int i, int j) {
+            const double x = j ? b.v[0][1] : b.v[0][0], y = j ? b.v[1][1] : b.v[1][0];
+            return i ? y : x;
+        };
+        double c, s;
+        jacobi_rotation(side(X, sa, sa), side(Y, sb, sb), side(Z, sa, sb), c, s);
+        cs1[nx] = make_double2(c, s);
+        if (blockIdx.y == 0 && nx < IQ) rot[h + k1] = make_double2(c, s);
+    }
+#pragma unroll
+    for (int e = 0; e < BLOCKS; ++e) {
+        const int ip = t / SQ + TWO_T / SQ * e, iq = t % SQ;
+        const Block n = rotate_block(B[e], cs0[SQ + ip], cs0[iq], p_first + ip == q_first + iq);
+        T[2 * ip][iq] = make_double2(n.v[0][0], n.v[0][1]);
+        T[2 * ip + 1][iq] = make_double2(n.v[1][0], n.v[1][1]);
+    }
+    __syncthreads();
+    for (int i = t; i < IP * IQ; i += TWO_T) {
+        const int ip = i / IQ, iq = i % IQ, kp = p_first + 1 + ip, kq = q_first + 1 + iq;
+        if (kp >= h || kq >= h) continue;
+        const int2 lp = loc[IQ + ip], lq = loc[iq];
+        const double *row0 = reinterpret_cast<const double*>(T[lp.x]), *row1 = reinterpret_cast<const double*>(T[lp.y]);
+        const Block n = rotate_block({{{row0[lq.x], row0[lq.y]}, {row1[lq.x], row1[lq.y]}}}, cs1[IQ + ip], cs1[iq],
+                                     kp == kq);
+        int p0, p1, q0, q1;
+        jacobi_pair(N, r + 1, kp, p0, p1);
+        jacobi_pair(N, r + 1, kq, q0, q1);
+        Aout[int64_t(p0) * N + q0] = n.v[0][0];
+        Aout[int64_t(p0) * N + q1] = n.v[0][1];
+        Aout[int64_t(p1) * N + q0] = n.v[1][0];
+        Aout[int64_t(p1) * N + q1] = n.v[1][1];
     }
 }
 
@@ -553,6 +669,7 @@ saq_status run_jacobi(const double* C, int32_t n, double* w, double* V, void* ws
     double* part = reinterpret_cast<double*>(base + 4 * align256(el * 8));
     const unsigned gel = unsigned((el + 255) / 256);
     const dim3 gpair(unsigned((N / 2 + JQ - 1) / JQ), unsigned((N / 2 + JP - 1) / JP));
+    const dim3 gtwo(unsigned((N / 2 + IQ - 1) / IQ), unsigned((N / 2 + IP - 1) / IP));
     hipLaunchKernelGGL(jacobi_init_kernel, dim3(gel), dim3(256), 0, st, C, n, N, A[0], Vw);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_err(e, "jacobi_init_kernel launch");
@@ -560,9 +677,11 @@ saq_status run_jacobi(const double* C, int32_t n, double* w, double* V, void* ws
     int cur = 0;
     bool converged = false;
     for (int sweep = 0; sweep < JACOBI_MAX_SWEEPS && !converged; ++sweep) {
-        for (int r = 0; r + 1 < N; ++r) {
-            hipLaunchKernelGGL(jacobi_round_kernel, gpair, dim3(256), 0, st, A[cur], A[cur ^ 1],
-                               rot + int64_t(r) * (N / 2), N, r);
+        // an odd number of rounds: two at a time, then the last
+        for (int r = 0; r + 1 < N; r += 2) {
+            double2* rr = rot + int64_t(r) * (N / 2);
+            if (r + 2 < N) hipLaunchKernelGGL(jacobi_two_kernel, gtwo, dim3(TWO_T), 0, st, A[cur], A[cur ^ 1], rr, N, r);
+            else hipLaunchKernelGGL(jacobi_round_kernel, gpair, dim3(256), 0, st, A[cur], A[cur ^ 1], rr, N, r);
             cur ^= 1;
         }
         launch_vectors(rot, Vw, N, st);

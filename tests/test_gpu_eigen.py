@@ -46,3 +46,10 @@ def test_sym_eigen_edges(n, kind):
     orth = float((V.T.contiguous() @ V - torch.eye(n, dtype=torch.float64, device=cuda())).abs().max())
     say(f"  residual {res:.1e} orthogonality {orth:.1e} (within {tol:.1e})")
     assert res < tol and orth < tol
+
+
+@pytest.mark.parametrize("n", [4, 5, 6, 8, 59, 60, 61, 62, 63, 64, 65, 123, 124, 125, 126, 187, 240, 250])
+def test_sym_eigen_pair_tiles(n):
+    """Around the 30 row and 62 column pairs that a workgroup takes through two
+    rounds at once."""
+    test_sym_eigen_edges(n, "dense")
