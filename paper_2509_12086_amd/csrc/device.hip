@@ -932,9 +932,8 @@ __global__ __launch_bounds__(256, 2) void fused_encode_kernel(const FusedArgs ar
 // The queries are split once per scan (split_query_kernel) when a
 // segment's first kept column is a multiple of 8, else while staging.  A
 // segment whose width is not a multiple of 32 pads its last k-step with
-// zeros on the record side.  Segments of at most 8 bits unpack a plane
-// byte (8 dims) with one lookup in a 256-entry table that spreads its bits
-// to one bit per byte.  With prefix b > 0 a segment reads only its
+// zeros on the record side.  Codes are unpacked by an 8 x 8 bit
+// transposition of their planes (plane_bytes).  With prefix b > 0 a segment reads only its
 // first min(b, B) bit planes, the b-bit prefix floor(c / 2^(B-b)) of every
 // code, and scales its factor by 2^(B-b) (progressive approximation).
 //
@@ -1052,6 +1051,46 @@ __device__ __forceinline__ float pair_segment(const uint8_t* __restrict__ rec, i
     return acc + acc2;
 }
 
+// Eight planes of 16 dims (plane words w[0..7], most significant first, dim d at
+// bit d of 16) as 16 bytes: an 8 x 8 bit transposition in each of the two bytes,
+// rows i and i + 4 of it in the halves of one word.  36 VALU operations whatever
+// the number of planes; a table of spread bytes took 5 per plane byte and an LDS
+// read, single bits 2 per plane and dim above 8 planes.  Multi-stage scan of 8
+// queries, 500,000 records of 1,536 dims: 386 us so, 373 now, 369 with the loads
+// of two steps at once (below); plain scans of narrow segments: 64 queries, 1M
+// records of 128 dims 222 and 213, 130 queries, 100,001 of 333 dims 171 and 146.
+// how: the plane words hold the lane's 16 dims (PLANES), or lane half h those of
+// the 32 dims of step h of a pair, both halves' dims (FIRST, SECOND of the pair).
+enum { PLANES, FIRST, SECOND };
+template <int HOW>
+__device__ __forceinline__ void plane_bytes(const uint32_t* w, uint32_t half_sel, uint32_t (&y)[4]) {
+    auto step_word = [](uint32_t x) {
+        const auto z = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        return uint32_t(z[HOW == SECOND ? 1 : 0]);
+    };
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        if (HOW == PLANES) y[j] = w[7 - j] | w[3 - j] << 16;
+        else y[j] = __builtin_amdgcn_perm(step_word(w[3 - j]), step_word(w[7 - j]), half_sel);
+        const uint32_t t = ((y[j] >> 12) ^ y[j]) & 0x0000f0f0u;
+        y[j] = y[j] ^ t ^ (t << 12);
+    }
+    auto swap = [&](int a, int b, int s, uint32_t m) {
+        const uint32_t u = y[a], v = y[b];
+        y[a] = (u & m) | ((v << s) & ~m);
+        y[b] = ((u >> s) & m) | (v & ~m);
+    };
+    swap(0, 2, 2, 0x33333333u);
+    swap(1, 3, 2, 0x33333333u);
+    swap(0, 1, 1, 0x55555555u);
+    swap(2, 3, 1, 0x55555555u);
+}
+// dim d's byte
+__device__ __forceinline__ float plane_byte(const uint32_t (&y)[4], int d) {
+    const int b = d & 7;
+    return float((y[b & 3] >> (8 * (2 * (b >> 2) + (d >> 3)))) & 0xffu);
+}
+
 __device__ __forceinline__ float pair_segment_any(int B, const uint8_t* __restrict__ rec, int W,
                                                   const float* __restrict__ qs, bool qvec,
                                                   const uint64_t* __restrict__ spread, int c0,
@@ -1092,7 +1131,7 @@ __global__ __launch_bounds__(256, (MS || TR) ? 3 : 4) void estimate_kernel(
     const float* __restrict__ lbq, const float* __restrict__ qsum, const float* __restrict__ tau,
     uint8_t* __restrict__ stage, float* __restrict__ out, const u32x4* __restrict__ Qs, int qg) {
     __shared__ __attribute__((aligned(16))) float lds[EST_LDS_FLOATS];
-    __shared__ uint64_t spread[256];      // bit i of the index -> bit 8 i
+    __shared__ uint64_t spread[MS ? 256 : 1];   // bit i of the index -> bit 8 i
     // multi-stage: open-pair counts of alternate bound checks, list fills
     __shared__ int ms_open[2], ms_fill[2];
     // query slice term tm of buffer b, query row q, dims d..d+7: 16 bytes at
@@ -1103,7 +1142,7 @@ __global__ __launch_bounds__(256, (MS || TR) ? 3 : 4) void estimate_kernel(
     };
     static_assert(!(TR && MS), "the multi-stage scan keeps records as the A operand");
     const int t = threadIdx.x;
-    {
+    if constexpr (MS) {
         uint64_t v = 0;
 #pragma unroll
         for (int i = 0; i < 8; ++i) v |= uint64_t((t >> i) & 1) << (8 * i);
@@ -1180,10 +1219,25 @@ __global__ __launch_bounds__(256, (MS || TR) ? 3 : 4) void estimate_kernel(
 #pragma unroll
         for (int tm = 0; tm < 3; ++tm) g.q[tm] = qlive ? src[tm] : u32x4{0u, 0u, 0u, 0u};
     };
+    // whole 64-dim runs of a segment are fetched at their first k-step, lane
+    // half h the 4 bytes per plane of step h (each 2-byte load of one step's
+    // took as much of the texture addresser, 64 lines, as these for two)
+    auto paired = [](int W, int j0) { return (j0 & ~63) + 64 <= W; };
+    const uint32_t half_sel = uh ? 0x07060302u : 0x05040100u;
     auto fetch = [&](Raw& g, int si, int j0) {
         const SegEntry e = segs[si];
         const int W = e.width, B = used_bits(e.bits);
-        fetch_planes(g, e, B, j0 + 16 * uh);
+        if (!paired(W, j0)) {
+            fetch_planes(g, e, B, j0 + 16 * uh);
+        } else if ((j0 & 32) == 0) {
+            const int pb = (W + 7) >> 3;
+            const uint8_t* pl = rec + e.code_off + (j0 >> 3) + 4 * uh;
+#pragma unroll
+            for (int p = 0; p < 16; ++p) {
+                g.w[p] = 0u;
+                if (p < B) __builtin_memcpy(&g.w[p], pl + int64_t(p) * pb, 4);
+            }
+        }
         if ((e.col & 7) == 0) {
             fetch_query(g, e.col + j0);
         } else {
@@ -1206,40 +1260,30 @@ __global__ __launch_bounds__(256, (MS || TR) ? 3 : 4) void estimate_kernel(
     };
     // this lane's operand from its 16 dims d0 .. d0 + 15 of a segment of
     // width W read at B bits (zero past W), and the staged query slice
-    auto put_core = [&](const Raw& g, int W, int B, int d0, int buf) {
-        uint32_t c[16];
-        // loops fully unrolled with a uniform predicate per plane, so g stays
-        // in registers (a loop exit would index it dynamically)
-        if (B <= 8) {
-            // codes as the bytes of two words: each plane byte is spread to
-            // one bit per byte by the table and shifted in (a code below
-            // 2^8 never carries into the next byte)
-            uint64_t lo = 0, hi = 0;
-#pragma unroll
-            for (int p = 0; p < 8; ++p) {
-                if (p < B) {
-                    lo = (lo << 1) | spread[g.w[p] & 0xffu];
-                    hi = (hi << 1) | spread[(g.w[p] >> 8) & 0xffu];
-                }
-            }
-#pragma unroll
-            for (int d = 0; d < 8; ++d) {
-                c[d] = uint32_t(lo >> (8 * d)) & 0xffu;
-                c[8 + d] = uint32_t(hi >> (8 * d)) & 0xffu;
-            }
-        } else {
-#pragma unroll
-            for (int d = 0; d < 16; ++d) c[d] = 0u;
-#pragma unroll
-            for (int p = 0; p < 16; ++p) {
-                if (p < B) {
-#pragma unroll
-                    for (int d = 0; d < 16; ++d) c[d] = (c[d] << 1) | ((g.w[p] >> d) & 1u);
-                }
-            }
-        }
-        // f_s (c - h) with h = (2^B - 1)/2; c - h is exact in FP32
+    auto put_core = [&](const Raw& g, int W, int B, int d0, int buf, int how) {
+        // the codes' first 8 planes as bytes, top bits first (planes past B are
+        // zero), and what is left of them above 8 bits; f_s (c - h) with
+        // h = (2^B - 1)/2: every sum below is exact in FP32
+        uint32_t top[4], low[4];
+        auto bytes = [&](const uint32_t* w, uint32_t (&y)[4]) {
+            if (PK || how == PLANES) plane_bytes<PLANES>(w, half_sel, y);
+            else if (how == FIRST) plane_bytes<FIRST>(w, half_sel, y);
+            else plane_bytes<SECOND>(w, half_sel, y);
+        };
+        bytes(g.w, top);
         const float h = 0.5f * float((1 << B) - 1);
+        float ch[16];
+        if (B <= 8) {
+            const float scale = ldexpf(1.f, B - 8);
+#pragma unroll
+            for (int d = 0; d < 16; ++d) ch[d] = fmaf(plane_byte(top, d), scale, -h);
+        } else {
+            bytes(g.w + 8, low);
+            const float scale = ldexpf(1.f, B - 8), rest = ldexpf(1.f, B - 16);
+#pragma unroll
+            for (int d = 0; d < 16; ++d)
+                ch[d] = fmaf(plane_byte(top, d), scale, fmaf(plane_byte(low, d), rest, -h));
+        }
         float a[16];
         if constexpr (TR) {
             // c - h alone: 2c - (2^B - 1) is an odd integer below 2^B, so
@@ -1247,7 +1291,7 @@ __global__ __launch_bounds__(256, (MS || TR) ? 3 : 4) void estimate_kernel(
             // for B <= 8 and as two (the rest below half an ulp of the
             // first) for B <= 16
 #pragma unroll
-            for (int d = 0; d < 16; ++d) a[d] = (use && d0 + d < W) ? float(c[d]) - h : 0.f;
+            for (int d = 0; d < 16; ++d) a[d] = (use && d0 + d < W) ? ch[d] : 0.f;
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
                 uint32_t t0[4];
@@ -1265,7 +1309,7 @@ __global__ __launch_bounds__(256, (MS || TR) ? 3 : 4) void estimate_kernel(
             }
         } else {
 #pragma unroll
-            for (int d = 0; d < 16; ++d) a[d] = (d0 + d < W) ? g.fs * (float(c[d]) - h) : 0.f;
+            for (int d = 0; d < 16; ++d) a[d] = (d0 + d < W) ? g.fs * ch[d] : 0.f;
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
                 uint32_t t0[4], t1[4], t2[4];
@@ -1281,7 +1325,8 @@ __global__ __launch_bounds__(256, (MS || TR) ? 3 : 4) void estimate_kernel(
     };
     auto put = [&](const Raw& g, int si, int j0, int buf) {
         const SegEntry e = segs[si];
-        put_core(g, e.width, used_bits(e.bits), j0 + 16 * uh, buf);
+        put_core(g, e.width, used_bits(e.bits), j0 + 16 * uh, buf,
+                 !paired(e.width, j0) ? PLANES : (j0 & 32) == 0 ? FIRST : SECOND);
     };
     // Packed k-steps (PK, plain scans of plans whose kept widths are all
     // multiples of 16): step kk covers kept dims EK kk .. EK kk + EK - 1
@@ -1319,7 +1364,7 @@ __global__ __launch_bounds__(256, (MS || TR) ? 3 : 4) void estimate_kernel(
             B = used_bits(e.bits);
             d0 = kd - e.col;
         }
-        put_core(g, W, B, d0, buf);
+        put_core(g, W, B, d0, buf, PLANES);
     };
 
     floatx16 acc[2];
