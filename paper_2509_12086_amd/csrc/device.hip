@@ -81,9 +81,8 @@ template <int BI> constexpr int gemm_rows() { return 64 * BI; }
 // Per buffer, LDS holds both operands as 16-byte chunks [A|B][term][k half]
 // [row]: a lane's MFMA operand (8 bf16 of one row, k half = lane / 32) is one
 // chunk, and a wave reads two contiguous 512-byte runs.  The X rows are split
-// as they are staged, thread t taking row t % (64 BI) and k half t / (64 BI),
-// so a wave writes 64 consecutive chunks; M comes pre-split from the plan in
-// the same chunk order, one 16-byte copy per chunk.
+// as they are staged; M comes pre-split from the plan in the same chunk order,
+// one 16-byte copy per chunk.
 //
 // A k-step has only 24 MFMAs per wave (768 cycles), too short to cover a
 // global load, so X and the B chunks are loaded two k-steps ahead into
@@ -116,27 +115,33 @@ __device__ __forceinline__ void gemm_split_tile_impl(
     const int ksteps = k_pad / SK;
 
     const int t = threadIdx.x;
-    // thread t stages XS values of A row t % RM in k half kh of the step (the
-    // same for the whole wave).  With EVEN every thread stages, four of the
-    // half's eight values (the norm's chain needs all eight, XL), and c comes
-    // with them: behind a branch on the thread the compiler cannot count the
-    // loads in flight and waits for all of them in every step, and a scalar
-    // load of c waits for its answer in the middle of one.  Larger tiles and
-    // those with per-row references gain nothing from it (their LDS reads and
-    // loads bound them).
+    // What a thread stages.  QUAD: four consecutive lanes take the 16 values of a
+    // row, so that a load instruction touches 16 lines instead of 64; with 128
+    // rows every thread has two of them.  Encode of 20,011 x 1536 688 -> 608 us of
+    // projection, 131,072 x 960 against references 1,643 -> 1,530; 128 x 128 tiles
+    // without references have no registers for the c that comes with it
+    // (1,350 -> 1,368) and load c as scalars.
+    // Otherwise (the norm's chain takes a row's eight values of a k half in order)
+    // thread t stages XS values of row t % RM in k half kh, the same for the whole
+    // wave; with EVEN every thread four of the eight it loads (XL): behind a
+    // branch on the thread the compiler cannot count the loads in flight and waits
+    // for all of them in every step.
     constexpr bool EVEN = BJ == 1 && !REF;
-    constexpr int XS = EVEN ? 4 : 8, XL = NORM ? 8 : XS;
-    const int lr = t % RM;
+    constexpr bool QUAD = !NORM && (BI == 1 || REF);
+    constexpr int XS = EVEN || (QUAD && BI == 1) ? 4 : 8, XL = NORM ? 8 : XS;
+    const int lr = QUAD ? t >> 2 : t % RM;
     const int kh = __builtin_amdgcn_readfirstlane((t / RM) & 1);
     const int h4 = __builtin_amdgcn_readfirstlane(EVEN ? t >> 7 : 0);
-    const int k8 = 8 * kh + (XL == 8 ? 0 : 4 * h4);
-    constexpr bool IN_STAGE = REF || EVEN;  // c is loaded beside X
-    const bool stager = EVEN || t < 2 * RM;
+    const int k8 = QUAD ? 4 * (t & 3) : 8 * kh + (XL == 8 ? 0 : 4 * h4);
+    constexpr bool IN_STAGE = REF || EVEN || QUAD;  // c is loaded beside X
+    const bool stager = EVEN || QUAD || t < 2 * RM;
     const int64_t arow = m0 + lr;
     const bool arow_ok = arow < n;
     // rows past n read row n-1 (always valid memory); their outputs and
     // norms are never stored
     const float* xrow = X + (arow_ok ? arow : n - 1) * int64_t(D);
+    const int64_t arow2 = std::min(arow + 64, n - 1);       // QUAD: a second row with 128
+    const float* xrow2 = X + arow2 * int64_t(D);
     // this thread copies B chunks t + 256 p of every k-step; a tile of 64 kept
     // dims takes its half of each 128 chunks, 384 of them, the last 128 by two
     // threads each
@@ -156,6 +161,14 @@ __device__ __forceinline__ void gemm_split_tile_impl(
         ref_bad = id < 0 || id >= R.K;
         crow = R.refs + int64_t(ref_bad ? 0 : id) * D;
     }
+    const float* crow2 = cp;
+    if (REF && QUAD && BI == 2) {
+        const int32_t id = R.ids != nullptr ? R.ids[arow2] : 0;
+        crow2 = R.refs + int64_t(id < 0 || id >= R.K ? 0 : id) * D;
+    }
+    // the group of 4 values q of what a thread stages
+    auto xq = [&](int q) { return QUAD ? (q ? xrow2 : xrow) : xrow + 4 * q; };
+    auto cq = [&](int q) { return QUAD ? (q ? crow2 : crow) : crow + 4 * q; };
     double nacc = 0.0;
 
     // raw global values, loaded two k-steps ahead into alternating register
@@ -168,10 +181,10 @@ __device__ __forceinline__ void gemm_split_tile_impl(
         if (stager && (decltype(fast)::value || kt < kfull)) {
 #pragma unroll
             for (int q = 0; q < XL / 4; ++q) {
-                const float4 x4 = *reinterpret_cast<const float4*>(xrow + kb + 4 * q);
+                const float4 x4 = *reinterpret_cast<const float4*>(xq(q) + kb);
                 g.x[4 * q + 0] = x4.x; g.x[4 * q + 1] = x4.y; g.x[4 * q + 2] = x4.z; g.x[4 * q + 3] = x4.w;
-                if (IN_STAGE) {
-                    const float4 c4 = *reinterpret_cast<const float4*>(crow + kb + 4 * q);
+                if (IN_STAGE && (REF || !QUAD || q == 0)) {
+                    const float4 c4 = *reinterpret_cast<const float4*>(cq(q) + kb);
                     g.c[4 * q + 0] = c4.x; g.c[4 * q + 1] = c4.y;
                     g.c[4 * q + 2] = c4.z; g.c[4 * q + 3] = c4.w;
                 }
@@ -179,9 +192,10 @@ __device__ __forceinline__ void gemm_split_tile_impl(
         } else if (stager) {
 #pragma unroll
             for (int e = 0; e < XL; ++e) {
-                g.x[e] = (kb + e < D) ? xrow[kb + e] : 0.f;
+                const int k = kb + (QUAD ? e & 3 : e), q = QUAD ? e >> 2 : 0;
+                g.x[e] = k < D ? xq(q)[k] : 0.f;
                 // the plan's c is zero padded to k_pad
-                if (IN_STAGE) g.c[e] = (!REF || kb + e < D) ? crow[kb + e] : 0.f;
+                if (IN_STAGE && (REF || !QUAD || q == 0)) g.c[e] = (!REF || k < D) ? cq(q)[k] : 0.f;
             }
         }
 #pragma unroll
@@ -194,7 +208,7 @@ __device__ __forceinline__ void gemm_split_tile_impl(
 #pragma unroll
             for (int e = 0; e < XL; ++e) {
                 // one uniform address, read as constant memory (scalar loads)
-                const float c = IN_STAGE ? g.c[e] : ccp[kb + e];
+                const float c = IN_STAGE ? g.c[QUAD && !REF ? e & 3 : e] : ccp[kb + e];
                 ra[e] = g.x[e] - c;
                 if (NORM) {
                     // exact (x - c)^2 in FP64; padding entries are 0 - 0
@@ -209,8 +223,16 @@ __device__ __forceinline__ void gemm_split_tile_impl(
             uint32_t a0[XS / 2], a1[XS / 2], a2[XS / 2];
 #pragma unroll
             for (int q = 0; q < XS / 2; ++q) split3(ra[2 * q], ra[2 * q + 1], a0[q], a1[q], a2[q]);
-            u32x4* A = L + buf * SCH + kh * RM + lr;
-            if constexpr (XS == 8) {
+            u32x4* A = L + buf * SCH + (QUAD ? (t & 3) >> 1 : kh) * RM + lr;
+            if constexpr (QUAD) {
+#pragma unroll
+                for (int q = 0; q < XS / 4; ++q) {
+                    u32x2* A2 = reinterpret_cast<u32x2*>(A + 64 * q) + (t & 1);
+                    A2[0] = u32x2{a0[2 * q], a0[2 * q + 1]};
+                    A2[4 * RM] = u32x2{a1[2 * q], a1[2 * q + 1]};
+                    A2[8 * RM] = u32x2{a2[2 * q], a2[2 * q + 1]};
+                }
+            } else if constexpr (XS == 8) {
                 A[0] = u32x4{a0[0], a0[1], a0[2], a0[3]};
                 A[2 * RM] = u32x4{a1[0], a1[1], a1[2], a1[3]};
                 A[4 * RM] = u32x4{a2[0], a2[1], a2[2], a2[3]};
