@@ -36,13 +36,13 @@ TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "encode_1Mx960_b4_hbm_counters.m
 
 
 def kernel_code_digest() -> str:
-    """sha256 of the encode kernels' code: csrc/device.hip followed by
-    csrc/plan.hpp with comments removed, every run of blanks in a line made
+    """sha256 of the encode kernels' code: csrc/device.hip, gemm_common.hpp and
+    plan.hpp with comments removed, every run of blanks in a line made
     one space and empty lines dropped, so that an edit of comments or of
     indentation keeps the digest and a change of code changes it."""
     return code_digest("\n".join(open(os.path.join(ROOT, "paper_2509_12086_amd", "csrc", f),
                                        encoding="utf-8").read()
-                                  for f in ("device.hip", "plan.hpp")))
+                                  for f in ("device.hip", "gemm_common.hpp", "plan.hpp")))
 
 
 def code_digest(src: str) -> str:
@@ -751,8 +751,10 @@ def multistage_timing(plan, Q, codes, fac, plain_out, ws, stream, k, m=4.0, sub=
 
 
 def scan_products_per_dim(plan, prefix_bits=0):
-    """bf16 matrix-core products the plain scan issues per kept dim and
-    query-record pair, averaged over the kept dims.  Plans whose kept widths
+    """bf16 matrix-core products per kept dim and query-record pair where the
+    plain scan runs on split operands (many queries over narrow segments; the
+    others run on the 8-bit integer cores, four digits a pass), averaged over
+    the kept dims.  Plans whose kept widths
     are all multiples of 16 and whose 32-dim steps would leave at least a
     quarter of the steps to padding take packed steps with the scaled codes
     split in three terms: six products.  Every other plan steps segment by
@@ -771,9 +773,9 @@ def scan_products_per_dim(plan, prefix_bits=0):
 def scan_leg(a):
     """Estimate scans (Section 3.2): 64 queries against 1M stored records
     encoded at 4 b/dim, for D = 128, 768, 1536 and 3072 (variance
-    exp(-8i/D)); the scan kernel contracts the records' codes with the
-    projected queries on the bf16 matrix cores at FP32 accuracy (exact
-    split operands; scan_products_per_dim gives the products issued)."""
+    exp(-8i/D)); the scan contracts the records' codes with the projected
+    queries on the 8-bit integer matrix cores, the queries as four exact 8-bit
+    digits (on the bf16 cores with exact split operands at D = 128)."""
     import torch
     import synth
     import paper_2509_12086_amd as saq
@@ -806,8 +808,6 @@ def scan_leg(a):
         row = {"D": ds.d, "D_kept": plan.D_kept, "code_bytes": plan.code_bytes,
                "ms_per_scan": ms, "tflops": flops / (ms * 1e-3) / 1e12,
                "frac_bf16_mfma": flops / (ms * 1e-3) / PEAK_BF16_MFMA,
-               "bf16_products_per_fp32_product": scan_products_per_dim(plan),
-               "issued_frac_bf16_mfma": scan_products_per_dim(plan) * flops / (ms * 1e-3) / PEAK_BF16_MFMA,
                "frac_fp32_mfma": flops / (ms * 1e-3) / PEAK_FP32_MFMA,
                "record_GBps": n * (plan.code_bytes + 4 * plan.n_factors) / (ms * 1e-3) / 1e9}
         if ds.d == 3072:

@@ -65,6 +65,7 @@ void build_staging(saq_plan& p) {
     // terms, in the GEMM's chunk order
     uint16_t* Ms = reinterpret_cast<uint16_t*>(p.staging.data() + L.off_Ms);
     const int ksteps = L.k_pad / kSplitK;
+#pragma omp parallel for collapse(2) schedule(static)
     for (int tile = 0; tile < L.n_pad / kGemmTileN; ++tile)
         for (int ks = 0; ks < ksteps; ++ks)
             for (int half = 0; half < 2; ++half)
@@ -621,14 +622,23 @@ void saq_plan::derive() {
     const int mode = params.projection_accumulation;
     acc64 = mode == 2 || (mode == 0 && (D > 1024 || max_kept_b >= 8));
     double most = 0.0;
+#pragma omp parallel for schedule(static) reduction(max : most)
     for (int r = 0; r < D_kept; ++r) {
         const float* row = M.data() + int64_t(r) * D;
-        double a[8] = {};                // independent sums, so that the loop vectorises
+        float f[16] = {};                // independent sums, so that the loop vectorises
         int k = 0;
-        for (; k + 8 <= D; k += 8)
-            for (int e = 0; e < 8; ++e) a[e] += double(row[k + e]) * row[k + e];
-        for (; k < D; ++k) a[0] += double(row[k]) * row[k];
-        most = std::max(most, ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7])));
+        for (; k + 16 <= D; k += 16)
+            for (int e = 0; e < 16; ++e) f[e] += row[k + e] * row[k + e];
+        double sum = 0.0;
+        for (float x : f) sum += double(x);
+        // FP32 squares are good to 2^-12 up to some 60,000 dims; outside their
+        // range once more in FP64
+        if (!(sum > 1e-20 && sum < 1e30) || D > 60000) {
+            sum = 0.0;
+            k = 0;
+        }
+        for (; k < D; ++k) sum += double(row[k]) * row[k];
+        most = std::max(most, sum);
     }
     m_exp = 0;
     if (most > 0.0 && std::isfinite(most)) (void)std::frexp(std::sqrt(most) * (1.0 + 1.0 / 512), &m_exp);
