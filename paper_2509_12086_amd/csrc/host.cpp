@@ -9,10 +9,10 @@
 #include <memory>
 #include <numeric>
 #include <string>
+#include <thread>
 #include <vector>
-#ifdef _OPENMP
+
 #include <omp.h>
-#endif
 
 #include "plan.hpp"
 
@@ -57,6 +57,27 @@ static float bf16_value(uint16_t h) {
     return f;
 }
 
+// Calls f(begin, end) over ranges that cover 0 .. n - 1, on the calling thread
+// and on threads that end with the call, `grain` items or more each.  Plans are
+// made and loaded in forked children too, where an OpenMP pool that the parent
+// has started is gone and a parallel region waits for it for good.  f must not
+// throw.
+template <class F>
+static void on_threads(int n, int grain, const F& f) {
+    const int parts = std::max(1, std::min({n / std::max(grain, 1), omp_get_max_threads(), 8}));
+    auto part = [&](int i) { f(int(int64_t(n) * i / parts), int(int64_t(n) * (i + 1) / parts)); };
+    std::vector<std::thread> threads;
+    int started = 0;
+    try {
+        threads.reserve(size_t(parts - 1));
+        for (; started < parts - 1; ++started) threads.emplace_back(part, started);
+    } catch (const std::exception&) {
+        // no memory or no thread for it: the rest runs here
+    }
+    for (int i = started; i < parts; ++i) part(i);
+    for (std::thread& t : threads) t.join();
+}
+
 void build_staging(saq_plan& p) {
     p.layout = device_layout(p);
     const DeviceLayout& L = p.layout;
@@ -65,22 +86,25 @@ void build_staging(saq_plan& p) {
     // terms, in the GEMM's chunk order
     uint16_t* Ms = reinterpret_cast<uint16_t*>(p.staging.data() + L.off_Ms);
     const int ksteps = L.k_pad / kSplitK;
-#pragma omp parallel for collapse(2) schedule(static)
-    for (int tile = 0; tile < L.n_pad / kGemmTileN; ++tile)
-        for (int ks = 0; ks < ksteps; ++ks)
-            for (int half = 0; half < 2; ++half)
-                for (int row = 0; row < kGemmTileN; ++row)
-                    for (int e = 0; e < 8; ++e) {
-                        const int r = tile * kGemmTileN + row, k = ks * kSplitK + 8 * half + e;
-                        float v = (r < p.D_kept && k < p.D) ? p.M[int64_t(r) * p.D + k] : 0.0f;
-                        for (int term = 0; term < 3; ++term) {
-                            const uint16_t h = bf16_rne(v);
-                            const int64_t chunk = (int64_t(tile) * ksteps + ks) * kSplitChunks +
-                                                  term * 2 * kGemmTileN + half * kGemmTileN + row;
-                            Ms[chunk * 8 + e] = h;
-                            v -= bf16_value(h);          // exact: the remainder fits in FP32
-                        }
+    auto chunk_rows = [&](int tile, int ks) {
+        for (int half = 0; half < 2; ++half)
+            for (int row = 0; row < kGemmTileN; ++row)
+                for (int e = 0; e < 8; ++e) {
+                    const int r = tile * kGemmTileN + row, k = ks * kSplitK + 8 * half + e;
+                    float v = (r < p.D_kept && k < p.D) ? p.M[int64_t(r) * p.D + k] : 0.0f;
+                    for (int term = 0; term < 3; ++term) {
+                        const uint16_t h = bf16_rne(v);
+                        const int64_t chunk = (int64_t(tile) * ksteps + ks) * kSplitChunks +
+                                              term * 2 * kGemmTileN + half * kGemmTileN + row;
+                        Ms[chunk * 8 + e] = h;
+                        v -= bf16_value(h);          // exact: the remainder fits in FP32
                     }
+                }
+    };
+    // 32 k-steps (65,536 entries) take some 0.2 ms, a thread's start 0.02
+    on_threads(L.n_pad / kGemmTileN * ksteps, 32, [&](int begin, int end) {
+        for (int i = begin; i < end; ++i) chunk_rows(i / ksteps, i % ksteps);
+    });
     float* c = reinterpret_cast<float*>(p.staging.data() + L.off_c);
     std::memcpy(c, p.c.data(), size_t(p.D) * 4);
     std::memcpy(p.staging.data() + L.off_seg, p.kept.data(), p.kept.size() * sizeof(SegEntry));
@@ -621,25 +645,28 @@ void saq_plan::derive() {
     // auto mode takes the FP64 totals there
     const int mode = params.projection_accumulation;
     acc64 = mode == 2 || (mode == 0 && (D > 1024 || max_kept_b >= 8));
-    double most = 0.0;
-#pragma omp parallel for schedule(static) reduction(max : most)
-    for (int r = 0; r < D_kept; ++r) {
-        const float* row = M.data() + int64_t(r) * D;
-        float f[16] = {};                // independent sums, so that the loop vectorises
-        int k = 0;
-        for (; k + 16 <= D; k += 16)
-            for (int e = 0; e < 16; ++e) f[e] += row[k + e] * row[k + e];
-        double sum = 0.0;
-        for (float x : f) sum += double(x);
-        // FP32 squares are good to 2^-12 up to some 60,000 dims; outside their
-        // range once more in FP64
-        if (!(sum > 1e-20 && sum < 1e30) || D > 60000) {
-            sum = 0.0;
-            k = 0;
+    std::vector<double> square(static_cast<size_t>(D_kept));
+    on_threads(D_kept, 1 + (1 << 17) / std::max(D, 1), [&](int begin, int end) {
+        for (int r = begin; r < end; ++r) {
+            const float* row = M.data() + int64_t(r) * D;
+            float f[16] = {};                // independent sums, so that the loop vectorises
+            int k = 0;
+            for (; k + 16 <= D; k += 16)
+                for (int e = 0; e < 16; ++e) f[e] += row[k + e] * row[k + e];
+            double sum = 0.0;
+            for (float x : f) sum += double(x);
+            // FP32 squares are good to 2^-12 up to some 60,000 dims; outside their
+            // range once more in FP64
+            if (!(sum > 1e-20 && sum < 1e30) || D > 60000) {
+                sum = 0.0;
+                k = 0;
+            }
+            for (; k < D; ++k) sum += double(row[k]) * row[k];
+            square[size_t(r)] = sum;
         }
-        for (; k < D; ++k) sum += double(row[k]) * row[k];
-        most = std::max(most, sum);
-    }
+    });
+    double most = 0.0;
+    for (double x : square) most = std::max(most, x);
     m_exp = 0;
     if (most > 0.0 && std::isfinite(most)) (void)std::frexp(std::sqrt(most) * (1.0 + 1.0 / 512), &m_exp);
     build_staging(*this);
