@@ -17,6 +17,9 @@ saq_status hip_status(hipError_t e, const char* what);
 inline const SegEntry* device_segments(const saq_plan* p) {
     return reinterpret_cast<const SegEntry*>(static_cast<const char*>(p->dev) + p->layout.off_seg);
 }
+inline const float* device_weights(const saq_plan* p) {
+    return reinterpret_cast<const float*>(static_cast<const char*>(p->dev) + p->layout.off_weight);
+}
 
 // Projected queries Qp [nq x max(D_kept, 1)] and ||q - c||^2 [nq], against
 // the plan's c or, when ref is given, against that one row.

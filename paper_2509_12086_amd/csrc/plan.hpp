@@ -19,12 +19,14 @@ namespace saq {
 //           the order the split-operand GEMM stages them in LDS
 //   c_pad   float [k_pad]
 //   segtab  int32 [n_kept x 4]      column start, width, bits, code byte offset
+//   weight  float [D_kept]          2^shift of the dim's segment
 //   S       float [sum_s W_s^2]     per kept segment, row-major W x W blocks
 //                                   sqrt(sigma_i^2) R_s^T (one float if absent)
 constexpr int kGemmTileN = 128;   // GEMM tile along the kept dims
 constexpr int kGemmTileK = 32;    // k_pad granularity: the GEMM's k-steps of 16 run in
                                   // pairs (32-wide k-tiles for FP64 totals)
 constexpr int kSplitK = 16;       // k-step of the split-operand GEMM
+constexpr int kMaxShift = 3;      // largest shift of a segment's query components
 constexpr int kSplitChunks = 3 * 2 * kGemmTileN;   // 16-byte chunks per tile and k-step
 
 struct SegEntry {
@@ -36,7 +38,7 @@ struct SegEntry {
 
 struct DeviceLayout {
     int32_t n_pad = 0, k_pad = 0;
-    int64_t off_Ms = 0, off_c = 0, off_seg = 0, off_S = 0, bytes = 0;
+    int64_t off_Ms = 0, off_c = 0, off_seg = 0, off_weight = 0, off_S = 0, bytes = 0;
 };
 
 }  // namespace saq
@@ -61,8 +63,12 @@ struct saq_plan {
     // derived
     int32_t D_kept = 0, n_kept = 0, max_kept_w = 0, max_kept_b = 0;
     bool acc64 = false;                  // projection accumulates k-tiles into FP64
-    int m_exp = 0;                       // every row of M has a norm below 2^m_exp, with a
-                                         // 2^-9 margin for the projection's rounding
+    bool even_rows = true;               // no row of M is longer than 8 times another
+                                         // (rows of zeros aside)
+    // The integer scan's fixed point holds the query components of kept segment
+    // s times 2^shift[s], 0 .. kMaxShift: fewer bits go unused where the dims
+    // spread less.
+    std::vector<int32_t> shift;
     int64_t code_bytes = 0;
     std::vector<saq::SegEntry> kept;
 

@@ -8,10 +8,15 @@
 // per pass as they are stored, so they need no conversion to floating point,
 // and a query is written once per scan as four signed 8-bit digits of a
 // 31-bit fixed-point number,
-//   q'_j = 2^(e - 30) (2^24 d0 + 2^16 d1 + 2^8 d2 + d3),   2^e > ||q - c|| max_j ||M_j||,
-// so that |q'_j| < 2^e: rounded to at most 2^-29 ||q - c|| for an orthonormal
-// M, far below FP32's rounding of the estimate.  The 32-bit integer sums
-// over a segment carry no rounding at all; FP32 enters where a segment ends.
+//   q'_j = 2^(e - k_s - 30) (2^24 d0 + 2^16 d1 + 2^8 d2 + d3),   2^(e - 1) <= max_j 2^k_s |q'_j| < 2^e,
+// with the query's exponent e and shifts k_s of the plan's segments, which
+// follow the spread of their dims: components are
+// rounded to at most 2^(3 - 30) of the largest, and to 2^-30 of it where they
+// are as large; 2^-27 ||q - c|| ||o|| in all for an orthonormal M, an eighth
+// of FP32's rounding of the estimate, and far less for queries spread like the
+// data.  Plans whose rows of M differ in length run on split bf16 operands
+// (even_rows).  The 32-bit integer sums over a segment carry no rounding at
+// all; FP32 enters where a segment ends.
 //
 // Codes as bytes.  A pass covers at most 8 bit planes of one segment.  With
 // b < 8 planes the byte holds the code in its top bits, the first plane
@@ -92,13 +97,32 @@ struct Pass {
 constexpr int ARG_PASSES = 96;
 struct PassArg { Pass p[ARG_PASSES]; };
 
-// The exponent e of a query's fixed point from its squared norm and the plan's
-// bound on the rows of M.  Norms below 2^-70 (their squares leave FP32's range)
-// count as 2^-70.
-__device__ __forceinline__ int query_exponent(float norm2, int m_exp) {
+// The exponent e of a query whose largest weighted component is v.  A pass's
+// sums, below 2^46 in units of 2^(e - 30), stay in FP32's range for every e.
+__device__ __forceinline__ int query_exponent(float v) {
     int k = 0;
-    if (norm2 < __builtin_inff()) (void)frexpf(fmaxf(norm2, 0x1p-140f), &k);
-    return m_exp + ((k + 1) >> 1);
+    (void)frexpf(v, &k);
+    return v > 0.f ? min(max(k, -96), 111) : -96;
+}
+
+// The largest weighted component of a row, over `lanes` lanes that start at
+// j0 = 0 .. lanes - 1 (a power of two of a wave's; all of them get it).
+__device__ __forceinline__ float largest(const float* __restrict__ row, const float* __restrict__ weight, int dk,
+                                         int j0, int lanes) {
+    float v = 0.f;
+    if ((dk & 3) == 0) {        // rows and weights start at 16-byte addresses
+#pragma unroll 4
+        for (int j = 4 * j0; j < dk; j += 4 * lanes) {
+            const float4 x = *reinterpret_cast<const float4*>(row + j), w = *reinterpret_cast<const float4*>(weight + j);
+            v = fmaxf(fmaxf(v, fmaxf(fabsf(x.x * w.x), fabsf(x.y * w.y))),
+                      fmaxf(fabsf(x.z * w.z), fabsf(x.w * w.w)));
+        }
+    } else {
+#pragma unroll 8
+        for (int j = j0; j < dk; j += lanes) v = fmaxf(v, fabsf(row[j] * weight[j]));
+    }
+    for (int d = 1; d < lanes; d <<= 1) v = fmaxf(v, __shfl_xor(v, d));
+    return v;
 }
 
 // Further passes of a scan with more than ARG_PASSES.
@@ -114,7 +138,8 @@ __global__ __launch_bounds__(64) void write_passes_kernel(const PassArg arg, int
 // of a plane word); with `few` (scan_few_kernel) [step][digit][quarter 2 m +
 // lh][query], dim 16 (2 m + lh) + 8 (kk % 2) + kk / 2.  Dims past the segment
 // are zero, so whatever the record side holds there adds nothing.  One
-// workgroup per step and query tile, one thread per query, m and lh.
+// workgroup per step and DQ queries, which first takes their exponents, then
+// one thread per query, m, lh and group of 4 kk.
 //
 // EXTRA more workgroups per query tile, a wave per query, write the queries'
 // exponents qexp and, per segment that has passes of 8 planes, half the sum of
@@ -122,32 +147,33 @@ __global__ __launch_bounds__(64) void write_passes_kernel(const PassArg arg, int
 // tiles' codes (last_bytes) to `tail`, which has room behind them, and write
 // the scan's first passes.
 constexpr int EXTRA = TQ / 4;
+constexpr int DQ = 16;
 __global__ __launch_bounds__(256) void query_digits_kernel(const float* __restrict__ Qp, int nq, int dk,
                                                            const SegEntry* __restrict__ segs, int n_kept,
-                                                           int prefix, const float* __restrict__ qn2,
-                                                           int m_exp, int tq, int few, int steps,
-                                                           u32x4* __restrict__ Qd, int* __restrict__ qexp,
+                                                           const float* __restrict__ weight, int prefix,
+                                                           int tq, int few, int steps,
+                                                           uint32_t* __restrict__ Qd, int* __restrict__ qexp,
                                                            float* __restrict__ qh,
                                                            const uint8_t* __restrict__ last,
                                                            int last_bytes, uint8_t* __restrict__ tail,
                                                            const PassArg arg, int count,
                                                            Pass* __restrict__ passes) {
-    const int step = blockIdx.x, q0 = blockIdx.y * tq;
+    const int parts = tq / DQ, step = blockIdx.x / parts, q0 = blockIdx.y * tq;
     if (step >= steps) {
-        const int extra = step - steps, b = extra * gridDim.y + blockIdx.y;
+        const int extra = blockIdx.x - steps * parts, b = extra * gridDim.y + blockIdx.y;
         for (int i = b * 256 + threadIdx.x; i < last_bytes; i += EXTRA * gridDim.y * 256) tail[i] = last[i];
         if (b == 0)
             for (int i = threadIdx.x; i < count; i += 256) passes[i] = arg.p[i];
         const int r = extra * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, q = q0 + r;
         if (r >= tq || q >= nq) return;
         const float* row = Qp + int64_t(q) * dk;
-        const int e = query_exponent(qn2[q], m_exp);
+        const int e = query_exponent(largest(row, weight, dk, lane, 64));
         if (lane == 0) qexp[q] = e;
         for (int s = 0; s < n_kept; ++s) {
             const SegEntry g = segs[s];
             if (used_bits(g.bits, prefix) < 8) continue;
             int64_t sum = 0;
-            for (int j = lane; j < g.width; j += 64) sum += fixed_point(row[g.col + j], e);
+            for (int j = lane; j < g.width; j += 64) sum += fixed_point(row[g.col + j] * weight[g.col + j], e);
 #pragma unroll
             for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
             if (lane == 0) qh[s * padded_queries(nq) + q] = 0.5f * float(sum);
@@ -155,36 +181,48 @@ __global__ __launch_bounds__(256) void query_digits_kernel(const float* __restri
         return;
     }
     const int rows = min(tq, nq - q0);          // queries of this tile
+    const int first = blockIdx.x % parts * DQ;  // of this workgroup
+    if (first >= rows) return;
+    __shared__ int exps[DQ];
     int s = 0, st = step;
     while (st >= seg_steps(segs[s].width)) st -= seg_steps(segs[s++].width);
     const SegEntry g = segs[s];
-    const int q = threadIdx.x >> 2, m = (threadIdx.x >> 1) & 1, lh = threadIdx.x & 1;
-    if (q >= rows) return;
-    const float* row = Qp + int64_t(q0 + q) * dk + g.col;
-    const int e = query_exponent(qn2[q0 + q], m_exp);
-    uint32_t w[ND][4];
+    const int v = threadIdx.x & 3, lh = (threadIdx.x >> 2) & 1, m = (threadIdx.x >> 3) & 1, q = threadIdx.x >> 4;
+    const float* row = Qp + int64_t(q0 + min(first + q, rows - 1)) * dk + g.col;
+    const float scale = weight[g.col];          // one weight per segment
+    float x4[4];                                // loaded beside the exponents' components
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
+    for (int k = 0; k < 4; ++k) {
+        const int j = SD * st + (few ? 16 * (2 * m + lh) + 8 * (k & 1) + 2 * v + (k >> 1)
+                                     : 32 * lh + 8 * k + 4 * m + v);
+        x4[k] = j < g.width ? row[j] * scale : 0.f;
+    }
+    {
+        // 16 lanes per query; all 64 of a wave where there are at most 4
+        const int lanes = rows <= 4 ? 64 : 16, i = threadIdx.x / lanes;
+        const float most = largest(Qp + int64_t(q0 + min(first + i, rows - 1)) * dk, weight, dk,
+                                   threadIdx.x % lanes, lanes);
+        if (threadIdx.x % lanes == 0) exps[i] = query_exponent(most);
+    }
+    __syncthreads();
+    if (first + q >= rows) return;
+    const int e = exps[q];
+    uint32_t w[ND] = {};
 #pragma unroll
-        for (int d = 0; d < ND; ++d) w[d][v] = 0u;
+    for (int k = 0; k < 4; ++k) {
+        int x = fixed_point(x4[k], e);
+        // balanced digits, least significant first
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int j = SD * st + (few ? 16 * (2 * m + lh) + 8 * (k & 1) + 2 * v + (k >> 1)
-                                         : 32 * lh + 8 * k + 4 * m + v);
-            int x = j < g.width ? fixed_point(row[j], e) : 0;
-            // balanced digits, least significant first
-#pragma unroll
-            for (int d = ND - 1; d >= 0; --d) {
-                const int b = int(int8_t(x));
-                w[d][v] |= uint32_t(b & 0xff) << (8 * k);
-                x = (x - b) >> 8;
-            }
+        for (int d = ND - 1; d >= 0; --d) {
+            const int b = int(int8_t(x));
+            w[d] |= uint32_t(b & 0xff) << (8 * k);
+            x = (x - b) >> 8;
         }
     }
-    u32x4* dst = Qd + ((int64_t(blockIdx.y) * steps * tq + int64_t(step) * rows) * 4 * ND) +
-                 (m * 2 + lh) * rows + q;
+    uint32_t* dst = Qd + 4 * ((int64_t(blockIdx.y) * steps * tq + int64_t(step) * rows) * 4 * ND +
+                              (m * 2 + lh) * rows + first + q) + v;
 #pragma unroll
-    for (int d = 0; d < ND; ++d) dst[d * 4 * rows] = u32x4{w[d][0], w[d][1], w[d][2], w[d][3]};
+    for (int d = 0; d < ND; ++d) dst[d * 16 * rows] = w[d];
 }
 
 // Transposes, in each of the four byte lanes, the 8 x 8 bits of w[0..7]: bit
@@ -335,7 +373,8 @@ struct FactorStage {
     }
 };
 
-// The four digit sums of a pair joined: T / 2^24 in units of 2^24 d0 + ...
+// The four digit sums of a pair joined, 2^24 s0 + 2^16 s1 + 2^8 s2 + s3: the
+// pairs in integers, then in FP32.
 __device__ __forceinline__ float join_digits(int s0, int s1, int s2, int s3) {
     return fmaf(float(s0 * 256 + s1), 65536.f, float(s2 * 256 + s3));
 }
@@ -692,7 +731,7 @@ std::vector<Pass> scan_passes(const saq_plan* p, int prefix) {
                 P.steps = std::min(FOLD_STEPS, steps - st0);
                 P.q0 = q0 + st0;
                 P.s = int(s);
-                P.wexp = g.bits - p0 - b + (b < 8 ? b - 8 : 0);
+                P.wexp = g.bits - p0 - b + (b < 8 ? b - 8 : 0) - p->shift[s];
                 P.info = b == 8 && st0 + P.steps == steps;
                 out.push_back(P);
             }
@@ -765,7 +804,8 @@ saq_status scan_impl(const saq_plan* p, const float* Q, int32_t nq, const float*
     if (ws_bytes < saq_estimate_workspace_bytes(p, nq)) return saq::fail(SAQ_EINVAL, "workspace too small");
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::vector<Pass> pv = scan_passes(p, prefix_bits);
-    if (narrow_passes(p, pv, nq))
+    // rows of M of different lengths: the operands that hold every component to 24 bits
+    if (!p->even_rows || narrow_passes(p, pv, nq))
         return saq::scan_split(p, Q, nq, ref, codes, factors, n, prefix_bits, out, ws, st);
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
     const ScanLayout L(p, nq);
@@ -805,9 +845,10 @@ saq_status scan_impl(const saq_plan* p, const float* Q, int32_t nq, const float*
         const int k = int(std::min<size_t>(ARG_PASSES, pv.size() - i));
         std::copy(pv.begin() + i, pv.begin() + i + k, arg.p);
         if (i == 0)
-            hipLaunchKernelGGL(query_digits_kernel, dim3(unsigned(steps + EXTRA), unsigned(qtiles)), dim3(256),
-                               0, st, Qp, nq, dk, segs, p->n_kept, int(prefix_bits), qn2, p->m_exp, tq,
-                               few ? 1 : 0, steps, Qd, qexp, qh, last, last_bytes, tail, arg, k, passes);
+            hipLaunchKernelGGL(query_digits_kernel, dim3(unsigned(steps * (tq / DQ) + EXTRA), unsigned(qtiles)),
+                               dim3(256), 0, st, Qp, nq, dk, segs, p->n_kept, saq::device_weights(p),
+                               int(prefix_bits), tq, few ? 1 : 0, steps, reinterpret_cast<uint32_t*>(Qd), qexp,
+                               qh, last, last_bytes, tail, arg, k, passes);
         else
             hipLaunchKernelGGL(write_passes_kernel, dim3(1), dim3(64), 0, st, arg, k, passes + i);
     }
