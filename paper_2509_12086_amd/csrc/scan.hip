@@ -75,8 +75,10 @@ inline __host__ __device__ int used_bits(int B, int prefix) {
     return (prefix > 0 && prefix < B) ? prefix : B;
 }
 
+// (past 2^e, and NaN: any value in range; see Largest)
 __device__ __forceinline__ int fixed_point(float v, int e) {
-    return int(rintf(ldexpf(v, QEXP - e)));
+    constexpr float most = float(1 << QEXP);
+    return int(fminf(fmaxf(rintf(ldexpf(v, QEXP - e)), -most), most));
 }
 
 // A pass: up to 8 bit planes of up to FOLD_STEPS steps of one segment.
@@ -98,31 +100,44 @@ constexpr int ARG_PASSES = 96;
 struct PassArg { Pass p[ARG_PASSES]; };
 
 // The exponent e of a query whose largest weighted component is v.  A pass's
-// sums, below 2^46 in units of 2^(e - 30), stay in FP32's range for every e.
+// sums, below 2^46 in units of 2^(e - 30), stay in FP32's range for every e (a
+// query with components past 2^111 has an infinite norm, and so the estimate).
 __device__ __forceinline__ int query_exponent(float v) {
+    if (!(v > 0x1p-97f)) return -96;
+    if (v >= 0x1p111f) return 111;
     int k = 0;
     (void)frexpf(v, &k);
-    return v > 0.f ? min(max(k, -96), 111) : -96;
+    return k;
 }
 
-// The largest weighted component of a row, over `lanes` lanes that start at
-// j0 = 0 .. lanes - 1 (a power of two of a wave's; all of them get it).
-__device__ __forceinline__ float largest(const float* __restrict__ row, const float* __restrict__ weight, int dk,
-                                         int j0, int lanes) {
+// The largest weighted component of a row, and whether all are finite, over
+// `lanes` lanes that start at j0 = 0 .. lanes - 1 (a power of two of a wave's; all
+// of them get it).  Fixed point has no infinities: a query with a component
+// that is not finite has NaN estimates, as FP32 sums over it would.
+struct Largest { float v; bool finite; };
+__device__ __forceinline__ Largest largest(const float* __restrict__ row, const float* __restrict__ weight, int dk,
+                                           int j0, int lanes) {
     float v = 0.f;
+    uint32_t bits = 0;          // of the largest |component|; infinity and NaN are past all finite ones
+    auto take = [&](float x, float w) {
+        v = fmaxf(v, fabsf(x * w));
+        bits = max(bits, __float_as_uint(x) & 0x7fffffffu);
+    };
     if ((dk & 3) == 0) {        // rows and weights start at 16-byte addresses
 #pragma unroll 4
         for (int j = 4 * j0; j < dk; j += 4 * lanes) {
             const float4 x = *reinterpret_cast<const float4*>(row + j), w = *reinterpret_cast<const float4*>(weight + j);
-            v = fmaxf(fmaxf(v, fmaxf(fabsf(x.x * w.x), fabsf(x.y * w.y))),
-                      fmaxf(fabsf(x.z * w.z), fabsf(x.w * w.w)));
+            take(x.x, w.x); take(x.y, w.y); take(x.z, w.z); take(x.w, w.w);
         }
     } else {
 #pragma unroll 8
-        for (int j = j0; j < dk; j += lanes) v = fmaxf(v, fabsf(row[j] * weight[j]));
+        for (int j = j0; j < dk; j += lanes) take(row[j], weight[j]);
     }
-    for (int d = 1; d < lanes; d <<= 1) v = fmaxf(v, __shfl_xor(v, d));
-    return v;
+    for (int d = 1; d < lanes; d <<= 1) {
+        v = fmaxf(v, __shfl_xor(v, d));
+        bits = max(bits, uint32_t(__shfl_xor(int(bits), d)));
+    }
+    return Largest{v, bits < 0x7f800000u};
 }
 
 // Further passes of a scan with more than ARG_PASSES.
@@ -153,7 +168,7 @@ __global__ __launch_bounds__(256) void query_digits_kernel(const float* __restri
                                                            const float* __restrict__ weight, int prefix,
                                                            int tq, int few, int steps,
                                                            uint32_t* __restrict__ Qd, int* __restrict__ qexp,
-                                                           float* __restrict__ qh,
+                                                           float* __restrict__ qh, float* __restrict__ qn2,
                                                            const uint8_t* __restrict__ last,
                                                            int last_bytes, uint8_t* __restrict__ tail,
                                                            const PassArg arg, int count,
@@ -167,8 +182,12 @@ __global__ __launch_bounds__(256) void query_digits_kernel(const float* __restri
         const int r = extra * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63, q = q0 + r;
         if (r >= tq || q >= nq) return;
         const float* row = Qp + int64_t(q) * dk;
-        const int e = query_exponent(largest(row, weight, dk, lane, 64));
-        if (lane == 0) qexp[q] = e;
+        const Largest most = largest(row, weight, dk, lane, 64);
+        const int e = query_exponent(most.v);
+        if (lane == 0) {
+            qexp[q] = e;
+            if (!most.finite) qn2[q] = __builtin_nanf("");
+        }
         for (int s = 0; s < n_kept; ++s) {
             const SegEntry g = segs[s];
             if (used_bits(g.bits, prefix) < 8) continue;
@@ -200,9 +219,9 @@ __global__ __launch_bounds__(256) void query_digits_kernel(const float* __restri
     {
         // 16 lanes per query; all 64 of a wave where there are at most 4
         const int lanes = rows <= 4 ? 64 : 16, i = threadIdx.x / lanes;
-        const float most = largest(Qp + int64_t(q0 + min(first + i, rows - 1)) * dk, weight, dk,
-                                   threadIdx.x % lanes, lanes);
-        if (threadIdx.x % lanes == 0) exps[i] = query_exponent(most);
+        const Largest most = largest(Qp + int64_t(q0 + min(first + i, rows - 1)) * dk, weight, dk,
+                                     threadIdx.x % lanes, lanes);
+        if (threadIdx.x % lanes == 0) exps[i] = query_exponent(most.v);
     }
     __syncthreads();
     if (first + q >= rows) return;
@@ -848,7 +867,7 @@ saq_status scan_impl(const saq_plan* p, const float* Q, int32_t nq, const float*
             hipLaunchKernelGGL(query_digits_kernel, dim3(unsigned(steps * (tq / DQ) + EXTRA), unsigned(qtiles)),
                                dim3(256), 0, st, Qp, nq, dk, segs, p->n_kept, saq::device_weights(p),
                                int(prefix_bits), tq, few ? 1 : 0, steps, reinterpret_cast<uint32_t*>(Qd), qexp,
-                               qh, last, last_bytes, tail, arg, k, passes);
+                               qh, qn2, last, last_bytes, tail, arg, k, passes);
         else
             hipLaunchKernelGGL(write_passes_kernel, dim3(1), dim3(64), 0, st, arg, k, passes + i);
     }

@@ -97,3 +97,30 @@ def test_small_components(bits, nq):
             fixed = 2.0 * np.abs(fu).sum(1) * 0.5 * unit[q] * 2.0 ** -min(s, 3)
             tol = 15 * 2.0 ** -24 * 2.0 * (np.abs(fu) @ np.abs(Q[q, cols])) + fixed
             assert np.all(np.abs(got - ref) <= tol), (s, q, np.max(np.abs(got - ref) / tol))
+
+
+@pytest.mark.parametrize("nq", [3, 12, 40])
+def test_queries_that_are_not_finite(nq):
+    """A query with an infinite or NaN entry has NaN estimates, whichever kernel
+    takes it, and its neighbours keep theirs to the bit; finite components whose
+    squares overflow give infinities."""
+    widths, bits = [80, 64, 99], [7, 9, 3]
+    rng = np.random.default_rng(nq)
+    D = sum(widths)
+    plan = saq.Plan.from_parts(widths, bits, np.eye(D, dtype=np.float32), np.zeros(D, np.float32)).upload(0)
+    codes = np.concatenate([rng.integers(0, 2 ** b, (150, w)) for w, b in zip(widths, bits)], 1).astype(np.int32)
+    packed = to_dev(oracle.pack(codes, widths, bits))
+    fac = to_dev((0.1 * rng.lognormal(0.0, 1.0, (150, 4))).astype(np.float32))
+    Q = rng.standard_normal((nq, D)).astype(np.float32)
+    want = saq.estimate_dist(plan, to_dev(Q), packed, fac)
+    rest = [q for q in range(nq) if q != 1]
+    for value, expect in ((np.nan, torch.isnan), (np.inf, torch.isnan), (-np.inf, torch.isnan),
+                          (1e20, torch.isposinf), (1e30, torch.isposinf), (-1e32, torch.isposinf)):
+        for where in (0, 100, D - 1):
+            P = Q.copy()
+            P[1, where] = value
+            got = saq.estimate_dist(plan, to_dev(P), packed, fac)
+            torch.cuda.synchronize()
+            say(f"  nq={nq} {value} at {where}: {got[1, :3].tolist()}")
+            assert bool(expect(got[1]).all())
+            assert torch.equal(got[rest], want[rest])
