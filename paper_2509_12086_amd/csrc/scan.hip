@@ -781,17 +781,23 @@ void group_passes(std::vector<Pass>& v, int nl) {
     }
 }
 
-// Many queries over plans of narrow segments run on split bf16 operands
-// instead (estimate_kernel), where f_s is part of the operand: here every pass
-// costs a 64-dim step and 6 VALU operations per pair whatever its width.
-// Measured at 64 queries and 1M records: 16-dim segments (D = 128) 319 us here
-// against 221 us there; 130 queries, 100,001 records, mostly 32-dim segments
-// (D = 333) 174 against 133 us; 64-dim segments (D = 768) 545 against 720 us.
-// Few queries cost a quarter of that per pass: D = 128 and one query, 123 us
-// against 152.
-bool narrow_passes(const saq_plan* p, const std::vector<Pass>& v, int nq) {
-    return nq > 16 && int64_t(p->D_kept) < 40 * int64_t(v.size());
+// Scans of narrow segments that scan_few_kernel does not take run on split bf16
+// operands instead (estimate_kernel), where f_s is part of the operand: in
+// scan_kernel every pass costs a 64-dim step and 6 VALU operations per pair
+// whatever its width.  Measured, us in scan_kernel / there: D = 128 (16-dim
+// segments) 68 / 60 at 16 queries and 300,000 records, 319 / 213 at 64 and 1M;
+// D = 200 84 / 71 at 9 to 16 queries and 300,000; D = 333 (mostly 32-dim segments)
+// 87 / 73 at 9 to 16 and 200,000, 174 / 146 at 130 and 100,001.  The line: 64
+// queries, 100,000 records, 32-dim segments 98 there, 118 at the commit before
+// this kernel; 40-dim segments 84 and 48-dim 74 here, 162 and 113 at that commit.
+// scan_few_kernel's passes cost a quarter: D = 128 and 12 queries 52 us, 62 there.
+bool narrow_passes(const saq_plan* p, const std::vector<Pass>& v) {
+    return int64_t(p->D_kept) < 40 * int64_t(v.size());
 }
+
+// Few queries, all digits resident in LDS (scan_few_kernel).
+size_t digit_bytes(const saq_plan* p, int nq) { return size_t(nq) * total_steps(p) * SD * ND; }
+bool few_queries(const saq_plan* p, int nq) { return nq <= 16 && digit_bytes(p, nq) <= RES_BYTES; }
 
 int64_t align16(int64_t v) { return (v + 15) & ~int64_t(15); }
 
@@ -824,7 +830,8 @@ saq_status scan_impl(const saq_plan* p, const float* Q, int32_t nq, const float*
     hipStream_t st = static_cast<hipStream_t>(stream);
     std::vector<Pass> pv = scan_passes(p, prefix_bits);
     // rows of M of different lengths: the operands that hold every component to 24 bits
-    if (!p->even_rows || narrow_passes(p, pv, nq))
+    const bool few = few_queries(p, nq);
+    if (!p->even_rows || (!few && narrow_passes(p, pv)))
         return saq::scan_split(p, Q, nq, ref, codes, factors, n, prefix_bits, out, ws, st);
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
     const ScanLayout L(p, nq);
@@ -841,9 +848,7 @@ saq_status scan_impl(const saq_plan* p, const float* Q, int32_t nq, const float*
     const int dk = p->D_kept, steps = total_steps(p);
     const int tq = nq <= TQ / 2 ? TQ / 2 : TQ;
     const int qtiles = (nq + tq - 1) / tq;
-    // few queries, all digits resident in LDS
-    const size_t resident = size_t(nq) * steps * SD * ND;
-    const bool few = nq <= 16 && resident <= RES_BYTES;
+    const size_t resident = digit_bytes(p, nq);
     // loads per group: what the longest pass needs, and where that is little
     // enough to cover several passes, so that a group's codes are in flight
     // for more than a step or two

@@ -59,3 +59,17 @@ def _agrees(plan, codes, fac, Q, got):
     err = np.max(np.abs(got.cpu().numpy() - ref) / scale)
     say(f"  error {err:.1e} of the scale")
     assert err < 2e-5
+
+
+@pytest.mark.parametrize("nq", [3, 6, 14, 16])
+@pytest.mark.parametrize("widths,bits", [([16] * 30, [4] * 30), ([24, 17, 16] * 12, [5, 9, 2] * 12)])
+def test_narrow_passes_of_few_queries(widths, bits, nq):
+    """Few queries whose digits do not fit in LDS take the same kernel as 32 of
+    them: narrow passes are slow in the other one from the first query on.  The
+    same kernel gives the same bits."""
+    plan, codes, packed, fac, Q = _case(widths, bits, 161, 32, nq + len(widths))
+    want = saq.estimate_dist(plan, to_dev(Q), to_dev(packed), to_dev(fac))
+    got = saq.estimate_dist(plan, to_dev(Q[:nq]), to_dev(packed), to_dev(fac))
+    torch.cuda.synchronize()
+    assert torch.equal(got, want[:nq])
+    _agrees(plan, codes, fac, Q, want)
