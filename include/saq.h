@@ -123,7 +123,8 @@ saq_status saq_covariance(const float* X_dev, int64_t n, int32_t D, int64_t fit_
    (round-robin) ordering, in FP64, run until the off-diagonal mass is below
    1e-15 of the diagonal's; SAQ_EINVAL if that takes more than 40 sweeps.
    The call waits for `stream` once per sweep.  ws_dev:
-   saq_sym_eigen_workspace_bytes(n) bytes (four n x n FP64 buffers). */
+   saq_sym_eigen_workspace_bytes(n) bytes (three n x n FP64 buffers); V_dev
+   holds intermediate values until the call has succeeded. */
 int64_t    saq_sym_eigen_workspace_bytes(int32_t n);
 saq_status saq_sym_eigen_device(const double* A_dev, int32_t n, double* w_dev, double* V_dev,
                                 void* ws_dev, int64_t ws_bytes, void* stream);

@@ -472,15 +472,16 @@ __global__ __launch_bounds__(TWO_T) void jacobi_two_kernel(const double* __restr
     }
 }
 
-// V <- V J for all the rounds of a sweep: the rows of V are independent, so a
-// workgroup keeps ROWS of them in LDS and applies the sweep's rotations, one
-// barrier per round and the next round's rotations in flight, instead of V
+// V <- V J for `rounds` rounds from r0 on, a sweep as a rule: the rows of V are
+// independent, so a workgroup keeps ROWS of them in LDS and applies the rounds'
+// rotations, one barrier per round and the next round's rotations in flight, instead of V
 // passing through memory in every round.  KM: pairs per thread.  ROWS = 0: one
 // row, in memory, for matrices whose rows LDS does not hold.  What bounds it is
 // the chain of a round: two LDS reads, four products, two writes, a barrier.
 template <int ROWS, int KM>
 __global__ __launch_bounds__(256) void jacobi_vectors_kernel(const double2* __restrict__ rot,
-                                                             double* __restrict__ V, int N) {
+                                                             double* __restrict__ V, int N, int r0,
+                                                             int rounds) {
     extern __shared__ double lv[];
     constexpr int R = ROWS ? ROWS : 1;
     const int h = N / 2, t = threadIdx.x;
@@ -504,8 +505,8 @@ __global__ __launch_bounds__(256) void jacobi_vectors_kernel(const double2* __re
         }
     };
     if constexpr (ROWS == 0) {
-        for (int r = 0; r + 1 < N; ++r) {
-            for (int k = t; k < h; k += 256) rotate(r, k, rot[int64_t(r) * h + k]);
+        for (int r = 0; r < rounds; ++r) {
+            for (int k = t; k < h; k += 256) rotate(r0 + r, k, rot[int64_t(r) * h + k]);
             __syncthreads();
         }
         return;
@@ -517,11 +518,11 @@ __global__ __launch_bounds__(256) void jacobi_vectors_kernel(const double2* __re
     };
     load(0, cur);
     __syncthreads();
-    for (int r = 0; r + 1 < N; ++r) {
-        load(std::min(r + 1, N - 2), nxt);
+    for (int r = 0; r < rounds; ++r) {
+        load(std::min(r + 1, rounds - 1), nxt);
 #pragma unroll
         for (int e = 0; e < KM; ++e)
-            if (t + 256 * e < h) rotate(r, t + 256 * e, cur[e]);
+            if (t + 256 * e < h) rotate(r0 + r, t + 256 * e, cur[e]);
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < KM; ++e) cur[e] = nxt[e];
@@ -629,19 +630,19 @@ saq_status run_covariance(const float* X, int64_t n, int32_t D, int64_t fit_samp
     return e == hipSuccess ? SAQ_OK : hip_err(e, "cov_reduce_kernel launch");
 }
 
-// two buffers of A, V, a sweep's rotations (n - 1 rounds of n / 2 pairs)
+// two buffers of A, V; the rotations go to the caller's V until it is written
 int64_t jacobi_bytes(int32_t n) {
     const int64_t N = n + (n & 1);
-    return 4 * align256(N * N * 8) + align256(int64_t(JACOBI_OFF_BLOCKS) * 2 * 8) + 256;
+    return 3 * align256(N * N * 8) + align256(int64_t(JACOBI_OFF_BLOCKS) * 2 * 8) + 256;
 }
 
-// V <- V J of one sweep
-void launch_vectors(const double2* rot, double* V, int N, hipStream_t st) {
+// V <- V J of rounds r0 .. r0 + rounds - 1
+void launch_vectors(const double2* rot, double* V, int N, int r0, int rounds, hipStream_t st) {
     const size_t row = size_t(N) * 8;
 #define SAQ_LAUNCH_V(ROWS, KM)                                                                      \
     hipLaunchKernelGGL((jacobi_vectors_kernel<ROWS, KM>),                                           \
                        dim3(unsigned((N + (ROWS ? ROWS : 1) - 1) / (ROWS ? ROWS : 1))), dim3(256),  \
-                       ROWS * row, st, rot, V, N)
+                       ROWS * row, st, rot, V, N, r0, rounds)
     // ROWS rows within 64 KB.  Few rows: a round's chain hardly depends on
     // them, and rows spread over more CUs (n = 960, a sweep: 693 us with 4,
     // 520 with 2, 477 with 1; 2 halves the reads of the rotations).
@@ -665,8 +666,18 @@ saq_status run_jacobi(const double* C, int32_t n, double* w, double* V, void* ws
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + 255) & ~uintptr_t(255));
     double* A[2] = {reinterpret_cast<double*>(base), reinterpret_cast<double*>(base + align256(el * 8))};
     double* Vw = reinterpret_cast<double*>(base + 2 * align256(el * 8));
-    double2* rot = reinterpret_cast<double2*>(base + 3 * align256(el * 8));
-    double* part = reinterpret_cast<double*>(base + 4 * align256(el * 8));
+    double* part = reinterpret_cast<double*>(base + 3 * align256(el * 8));
+    // The rotations of a sweep, N - 1 rounds of N doubles, wait in V, which is
+    // written at the end only: all of them for an even n, all but the last round
+    // for an odd one (or a V that is 8 bytes off).  A small n's fit in `part`, which
+    // is written and read after them.
+    double2* rot = reinterpret_cast<double2*>(part);
+    int64_t room = int64_t(JACOBI_OFF_BLOCKS) * 2 / N;
+    if (room < N - 1) {
+        const int64_t off = (reinterpret_cast<uintptr_t>(V) & 15) ? 1 : 0;
+        rot = reinterpret_cast<double2*>(V + off);
+        room = (int64_t(n) * n - off) / N;
+    }
     const unsigned gel = unsigned((el + 255) / 256);
     const dim3 gpair(unsigned((N / 2 + JQ - 1) / JQ), unsigned((N / 2 + JP - 1) / JP));
     const dim3 gtwo(unsigned((N / 2 + IQ - 1) / IQ), unsigned((N / 2 + IP - 1) / IP));
@@ -678,13 +689,19 @@ saq_status run_jacobi(const double* C, int32_t n, double* w, double* V, void* ws
     bool converged = false;
     for (int sweep = 0; sweep < JACOBI_MAX_SWEEPS && !converged; ++sweep) {
         // an odd number of rounds: two at a time, then the last
+        int r0 = 0;
         for (int r = 0; r + 1 < N; r += 2) {
-            double2* rr = rot + int64_t(r) * (N / 2);
-            if (r + 2 < N) hipLaunchKernelGGL(jacobi_two_kernel, gtwo, dim3(TWO_T), 0, st, A[cur], A[cur ^ 1], rr, N, r);
+            const int rounds = r + 2 < N ? 2 : 1;
+            if (r + rounds - r0 > room) {
+                launch_vectors(rot, Vw, N, r0, r - r0, st);
+                r0 = r;
+            }
+            double2* rr = rot + int64_t(r - r0) * (N / 2);
+            if (rounds == 2) hipLaunchKernelGGL(jacobi_two_kernel, gtwo, dim3(TWO_T), 0, st, A[cur], A[cur ^ 1], rr, N, r);
             else hipLaunchKernelGGL(jacobi_round_kernel, gpair, dim3(256), 0, st, A[cur], A[cur ^ 1], rr, N, r);
             cur ^= 1;
         }
-        launch_vectors(rot, Vw, N, st);
+        launch_vectors(rot, Vw, N, r0, N - 1 - r0, st);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_err(e, "jacobi_round_kernel launch");
         hipLaunchKernelGGL(jacobi_off_kernel, dim3(JACOBI_OFF_BLOCKS), dim3(256), 0, st, A[cur], N, part);
