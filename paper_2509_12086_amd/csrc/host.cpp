@@ -9,10 +9,10 @@
 #include <memory>
 #include <numeric>
 #include <string>
-#include <thread>
 #include <vector>
-
+#ifdef _OPENMP
 #include <omp.h>
+#endif
 
 #include "plan.hpp"
 
@@ -44,68 +44,54 @@ DeviceLayout device_layout(const saq_plan& p) {
 }
 
 // bf16 with round-to-nearest-even of a finite FP32 value (its upper 16 bits
-// after rounding), and the FP32 value of a bf16
-static uint16_t bf16_rne(float f) {
-    uint32_t u;
-    std::memcpy(&u, &f, 4);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return uint16_t(u >> 16);
-}
-static float bf16_value(uint16_t h) {
-    const uint32_t u = uint32_t(h) << 16;
+// after rounding), and the FP32 value of a bf16, as the bits of both
+static inline uint32_t bf16_rne(uint32_t u) { return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16; }
+static inline float float_of(uint32_t u) {
     float f;
     std::memcpy(&f, &u, 4);
     return f;
 }
-
-// Calls f(begin, end) over ranges that cover 0 .. n - 1, on the calling thread
-// and on threads that end with the call, `grain` items or more each.  Plans are
-// made and loaded in forked children too, where an OpenMP pool that the parent
-// has started is gone and a parallel region waits for it for good.  f must not
-// throw.
-template <class F>
-static void on_threads(int n, int grain, const F& f) {
-    const int parts = std::max(1, std::min({n / std::max(grain, 1), omp_get_max_threads(), 8}));
-    auto part = [&](int i) { f(int(int64_t(n) * i / parts), int(int64_t(n) * (i + 1) / parts)); };
-    std::vector<std::thread> threads;
-    int started = 0;
-    try {
-        threads.reserve(size_t(parts - 1));
-        for (; started < parts - 1; ++started) threads.emplace_back(part, started);
-    } catch (const std::exception&) {
-        // no memory or no thread for it: the rest runs here
-    }
-    for (int i = started; i < parts; ++i) part(i);
-    for (std::thread& t : threads) t.join();
+static inline uint32_t bits_of(float f) {
+    uint32_t u;
+    std::memcpy(&u, &f, 4);
+    return u;
 }
 
+// Runs on the calling thread: plans are made and loaded in forked children too,
+// where an OpenMP pool that the parent has started is gone and a parallel region
+// waits for it for good.  Eight entries at a time, in loops that the compiler
+// vectorises: 608 x 768 in 0.7 ms (1.8 entry by entry, 0.6 so on eight threads).
 void build_staging(saq_plan& p) {
     p.layout = device_layout(p);
     const DeviceLayout& L = p.layout;
     p.staging.assign(size_t(L.bytes), 0);
     // M_split: each entry of M, zero padded to [n_pad x k_pad], as three bf16
-    // terms, in the GEMM's chunk order
+    // terms, in the GEMM's chunk order (16-byte chunks of 8 entries; those past
+    // M's rows stay zero)
     uint16_t* Ms = reinterpret_cast<uint16_t*>(p.staging.data() + L.off_Ms);
     const int ksteps = L.k_pad / kSplitK;
-    auto chunk_rows = [&](int tile, int ks) {
-        for (int half = 0; half < 2; ++half)
-            for (int row = 0; row < kGemmTileN; ++row)
-                for (int e = 0; e < 8; ++e) {
-                    const int r = tile * kGemmTileN + row, k = ks * kSplitK + 8 * half + e;
-                    float v = (r < p.D_kept && k < p.D) ? p.M[int64_t(r) * p.D + k] : 0.0f;
-                    for (int term = 0; term < 3; ++term) {
-                        const uint16_t h = bf16_rne(v);
-                        const int64_t chunk = (int64_t(tile) * ksteps + ks) * kSplitChunks +
-                                              term * 2 * kGemmTileN + half * kGemmTileN + row;
-                        Ms[chunk * 8 + e] = h;
-                        v -= bf16_value(h);          // exact: the remainder fits in FP32
+    constexpr int ROWS = 8;     // at a time: whole lines of both sides stay in the first cache
+    for (int r0 = 0; r0 < p.D_kept; r0 += ROWS)
+        for (int k = 0; k < p.D; k += 8) {
+            const int have = std::min(8, p.D - k);
+            uint16_t* out = Ms + ((int64_t(r0 / kGemmTileN) * ksteps + k / kSplitK) * kSplitChunks +
+                                  k / 8 % 2 * kGemmTileN + r0 % kGemmTileN) * 8;
+            for (int r = r0; r < std::min(r0 + ROWS, p.D_kept); ++r, out += 8) {
+                float v[8] = {};
+                const float* m = p.M.data() + int64_t(r) * p.D + k;
+                if (have == 8) std::memcpy(v, m, sizeof v);
+                else std::memcpy(v, m, size_t(have) * 4);
+                for (int term = 0; term < 3; ++term) {
+                    uint16_t h[8];
+                    for (int e = 0; e < 8; ++e) {
+                        const uint32_t b = bf16_rne(bits_of(v[e]));
+                        h[e] = uint16_t(b);
+                        v[e] -= float_of(b << 16);   // exact: the remainder fits in FP32
                     }
+                    std::memcpy(out + term * 2 * kGemmTileN * 8, h, sizeof h);
                 }
-    };
-    // 32 k-steps (65,536 entries) take some 0.2 ms, a thread's start 0.02
-    on_threads(L.n_pad / kGemmTileN * ksteps, 32, [&](int begin, int end) {
-        for (int i = begin; i < end; ++i) chunk_rows(i / ksteps, i % ksteps);
-    });
+            }
+        }
     float* c = reinterpret_cast<float*>(p.staging.data() + L.off_c);
     std::memcpy(c, p.c.data(), size_t(p.D) * 4);
     std::memcpy(p.staging.data() + L.off_seg, p.kept.data(), p.kept.size() * sizeof(SegEntry));
@@ -658,17 +644,15 @@ void saq_plan::derive() {
     // 0.71, 256 0.72 / 0.73, 1,024 0.90 / 0.74, 16,384 10.8 / 4.2 (in a segment of its
     // own 10.2 / 0.74).  The line is at 8.
     std::vector<double> square(static_cast<size_t>(D_kept));
-    on_threads(D_kept, 1 + (1 << 17) / std::max(D, 1), [&](int begin, int end) {
-        for (int r = begin; r < end; ++r) {
-            const float* row = M.data() + int64_t(r) * D;
-            double f[8] = {};                // independent sums, so that the loop vectorises
-            int k = 0;
-            for (; k + 8 <= D; k += 8)
-                for (int e = 0; e < 8; ++e) f[e] += double(row[k + e]) * row[k + e];
-            for (; k < D; ++k) f[0] += double(row[k]) * row[k];
-            square[size_t(r)] = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
-        }
-    });
+    for (int r = 0; r < D_kept; ++r) {
+        const float* row = M.data() + int64_t(r) * D;
+        double f[8] = {};                // independent sums, so that the loop vectorises
+        int k = 0;
+        for (; k + 8 <= D; k += 8)
+            for (int e = 0; e < 8; ++e) f[e] += double(row[k + e]) * row[k + e];
+        for (; k < D; ++k) f[0] += double(row[k]) * row[k];
+        square[size_t(r)] = ((f[0] + f[1]) + (f[2] + f[3])) + ((f[4] + f[5]) + (f[6] + f[7]));
+    }
     even_rows = true;
     double least = std::numeric_limits<double>::infinity(), most = 0.0;
     for (double x : square) {
