@@ -347,12 +347,15 @@ typedef struct {
 #define SAQ_BATCH_GROUPED 1    /* two grouped launches */
 typedef struct {
     int32_t quant_waves;     /* grouped mode: waves (of 64 vectors) per quantize workgroup: 1, 2
-                                or 4 (0: 1); halved while their LDS code buffers exceed 64 KiB */
+                                or 4 (0: 1); halved while their LDS code buffers exceed 64 KiB.
+                                With 1, few vectors are quantized one wave each instead */
     int32_t gemm_xcd_order;  /* grouped mode: 1 XCD-aware projection tile order (default),
-                                0 row-major */
+                                0 row-major; no effect on few rows that run without tiles
+                                (tile_rows 0) */
     int32_t mode;            /* SAQ_BATCH_FUSED or SAQ_BATCH_GROUPED */
-    int32_t tile_rows;       /* projection tile rows: 0 auto, 64, or 128 (128 only when no
-                                dataset accumulates its projection in FP64 k-tile totals) */
+    int32_t tile_rows;       /* projection tile rows: 0 auto (grouped mode: also smaller tiles or
+                                none where rows are few), 64, or 128 (128 only when no dataset
+                                accumulates its projection in FP64 k-tile totals) */
     int32_t reserved;        /* must be 0 */
 } saq_batch_tuning;
 

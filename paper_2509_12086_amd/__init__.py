@@ -590,7 +590,9 @@ class BatchTuning:
     """Launch shape of saq_encode_batched (saq_batch_tuning): the mode (one
     persistent fused launch, or two grouped launches), the projection tile
     rows (0 auto, 64 or 128), and for the grouped mode the quantize waves
-    per workgroup and the projection tile order."""
+    per workgroup and the projection tile order.  tile_rows = 0 and
+    quant_waves = 1 leave small batches to the kernels for few rows and few
+    vectors; other values are obeyed."""
     quant_waves: int = 1
     gemm_xcd_order: bool = True
     mode: int = BATCH_FUSED

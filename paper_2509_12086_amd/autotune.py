@@ -3,7 +3,9 @@
 It picks the launch shape of saq_encode_batched for a batch by timing
 candidates on the batch itself (or on its first rows):
   * mode            one persistent fused launch, or two grouped launches
-  * tile_rows       projection tile rows: 128 (FP32 accumulation only) or 64
+  * tile_rows       projection tile rows: 128 (FP32 accumulation only) or 64;
+                    in grouped mode also 0, the library's own choice, which
+                    has other kernels for small batches
   * quant_waves     grouped mode: waves (64 vectors each) per quantize
                     workgroup: {1, 2, 4} (fewer when their LDS code buffers
                     would not fit)
@@ -40,13 +42,14 @@ def signature(entries, rounds: int) -> str:
 
 def candidates(entries=()) -> List[BatchTuning]:
     """Launch shapes for a batch: 128-row tiles only when no dataset takes
-    FP64 k-tile totals (those run the 64-row tile)."""
+    FP64 k-tile totals (those run the 64-row tile), and the grouped mode left
+    to the library."""
     any64 = any(bool(e[0].info["projection_fp64_totals"]) for e in entries)
     rows = (64,) if any64 else (128, 64)
     out = [BatchTuning(mode=BATCH_FUSED, tile_rows=r) for r in rows]
     out += [BatchTuning(mode=BATCH_GROUPED, tile_rows=r, quant_waves=w, gemm_xcd_order=x)
             for r in rows for w in (1, 2, 4) for x in (True, False)]
-    return out
+    return out + [BatchTuning(mode=BATCH_GROUPED)]
 
 
 def tune(entries, rounds: int = 4, reps: int = 2, sample_rows: int = 131072,

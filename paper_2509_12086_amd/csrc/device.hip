@@ -2136,8 +2136,10 @@ saq_status plan_batch(const saq_batch_item* items, int32_t count, int32_t rounds
     }
     B.f.ticket = reinterpret_cast<unsigned long long*>(base + take(8));
     B.f.count = B.g.count;
-    B.few = saq::few_vectors(B.item, B.q.count);
-    B.few_rows = saq::few_rows(B.rows, B.q.count);
+    // the kernels for few rows and few vectors, unless the caller asks for tiles or
+    // for workgroups of several waves
+    B.few = want == 1 && saq::few_vectors(B.item, B.q.count);
+    B.few_rows = rows_req == 0 && saq::few_rows(B.rows, B.q.count);
     B.ws_need = off + 256;
     return SAQ_OK;
 }
