@@ -257,7 +257,11 @@ saq_status saq_quantize(const saq_plan* plan, const float* O_dev, int64_t ld, in
 /* Estimated squared distances (Section 3.2, Eq. estimator_inner_product)
    between nq query rows Q_dev [nq x D] and n encoded records:
      dist2_dev[q * n + i] = ||o_i||^2 + ||q - c||^2 - 2 sum_s f_s <u_s, q'_s>,
-   q' = M (q - c).  ws_dev: saq_estimate_workspace_bytes(plan, nq) bytes. */
+   q' = M (q - c).  Query and code components meet as exact products, and sums
+   are rounded as FP32 ones are, so the error stays within a few 2^-24 of
+   ||o_i||^2 + ||q - c||^2 + 2 sum_s f_s sum_j |u_j q'_j| per segment.  A query
+   with a component that is not finite has NaN estimates.
+   ws_dev: saq_estimate_workspace_bytes(plan, nq) bytes. */
 int64_t    saq_estimate_workspace_bytes(const saq_plan* plan, int32_t nq);
 saq_status saq_estimate_dist(const saq_plan* plan, const float* Q_dev, int32_t nq,
                              const uint8_t* codes_dev, const float* factors_dev, int64_t n,

@@ -123,15 +123,17 @@ __device__ __forceinline__ Largest largest(const float* __restrict__ row, const 
         v = fmaxf(v, fabsf(x * w));
         bits = max(bits, __float_as_uint(x) & 0x7fffffffu);
     };
+    // clamped addresses instead of a branch per load, which would wait for each
     if ((dk & 3) == 0) {        // rows and weights start at 16-byte addresses
 #pragma unroll 4
-        for (int j = 4 * j0; j < dk; j += 4 * lanes) {
+        for (int i = 0; i < dk; i += 4 * lanes) {
+            const int j = min(i + 4 * j0, dk - 4);
             const float4 x = *reinterpret_cast<const float4*>(row + j), w = *reinterpret_cast<const float4*>(weight + j);
             take(x.x, w.x); take(x.y, w.y); take(x.z, w.z); take(x.w, w.w);
         }
     } else {
 #pragma unroll 8
-        for (int j = j0; j < dk; j += lanes) take(row[j], weight[j]);
+        for (int i = 0; i < dk; i += lanes) take(row[min(i + j0, dk - 1)], weight[min(i + j0, dk - 1)]);
     }
     for (int d = 1; d < lanes; d <<= 1) {
         v = fmaxf(v, __shfl_xor(v, d));
@@ -246,7 +248,8 @@ __global__ __launch_bounds__(256) void query_digits_kernel(const float* __restri
 
 // Transposes, in each of the four byte lanes, the 8 x 8 bits of w[0..7]: bit
 // b of byte k of w[i] becomes bit i of byte k of w[b].  Three rounds of
-// masked swaps, each a shift and a bit-field insert per word.
+// masked swaps, each a shift and a bit-field insert per word (the recursive
+// block swaps of Warren, Hacker's Delight, section 7-3).
 __device__ __forceinline__ void transpose_bits(uint32_t (&w)[8]) {
     auto swap = [&](int a, int b, int s, uint32_t m) {
         const uint32_t x = w[a], y = w[b];
@@ -590,8 +593,9 @@ __global__ __launch_bounds__(256, 2) void scan_kernel(
 // The scan of at most 16 queries whose digits all fit in RES_BYTES of LDS: no
 // barrier after the first, and 16 x 16 x 64 products, which leave a lane 4
 // sums per record block instead of 16 (a quarter of the registers and of the
-// work where a pass ends), so four workgroups per CU keep the record stream in
-// flight.  Lane: records lane % 16 and 16 + lane % 16 of the wave, dims
+// work where a pass ends), so that three workgroups per CU keep the record stream
+// in flight (four with FOUR and 4 loads, two with 8 loads and the queries' 20 KB
+// of LDS full).  Lane: records lane % 16 and 16 + lane % 16 of the wave, dims
 // 16 (lane / 16) .. + 15 of a step; the two records' 16-bit pieces of a plane
 // share a word, are transposed together and parted again.  FOUR: at most four
 // queries, each the operand's rows 4 q .. 4 q + 3, so that the first of a lane's
