@@ -52,6 +52,16 @@ def candidates(entries=()) -> List[BatchTuning]:
     return out + [BatchTuning(mode=BATCH_GROUPED)]
 
 
+def pick(table: Sequence[Tuple[BatchTuning, float]]) -> BatchTuning:
+    """The fastest launch shape, or the library's own choice where that is
+    within 1 % of it: two runs of a sample differ by 0.3 %, and a sample of
+    131,072 rows put the row-major tile order 0.2 % ahead where four whole
+    datasets (500,000 x 3072) take 259 ms with it and 250 with the default."""
+    best, ms = min(table, key=lambda r: r[1])
+    own = BatchTuning(mode=BATCH_GROUPED)
+    return own if any(t == own and x <= 1.01 * ms for t, x in table) else best
+
+
 def tune(entries, rounds: int = 4, reps: int = 2, sample_rows: int = 131072,
          cache_file: Optional[str] = None, verbose: bool = False
          ) -> Tuple[BatchTuning, List[Tuple[BatchTuning, float]]]:
@@ -86,7 +96,7 @@ def tune(entries, rounds: int = 4, reps: int = 2, sample_rows: int = 131072,
         table.append((t, ms))
         if verbose:
             print(f"  autotune {t} -> {ms:.3f} ms", flush=True)
-    best = min(table, key=lambda r: r[1])[0]
+    best = pick(table)
     _CACHE[sig] = best
     if cache_file:
         stored = _read_cache(cache_file) if os.path.exists(cache_file) else {}
