@@ -10,11 +10,10 @@
 // 31-bit fixed-point number,
 //   q'_j = 2^(e - k_s - 30) (2^24 d0 + 2^16 d1 + 2^8 d2 + d3),   2^(e - 1) <= max_j 2^k_s |q'_j| < 2^e,
 // with the query's exponent e and shifts k_s of the plan's segments, which
-// follow the spread of their dims: components are
-// rounded to at most 2^(3 - 30) of the largest, and to 2^-30 of it where they
-// are as large; 2^-27 ||q - c|| ||o|| in all for an orthonormal M, an eighth
-// of FP32's rounding of the estimate, and far less for queries spread like the
-// data.  Plans whose rows of M differ in length run on split bf16 operands
+// follow the spread of their dims: components are rounded to at most 2^(3 - 30)
+// of the largest, and to 2^-30 of it for queries spread like the data.  As
+// independent roundings add up that is 2^-27 ||q - c|| ||o|| at most for an
+// orthonormal M, an eighth of FP32's rounding of the estimate.  Plans whose rows of M differ in length run on split bf16 operands
 // (even_rows).  The 32-bit integer sums over a segment carry no rounding at
 // all; FP32 enters where a segment ends.
 //
@@ -412,11 +411,12 @@ __device__ __forceinline__ float join_digits(int s0, int s1, int s2, int s3) {
 // step after next are fetched while the next step runs, and a group's codes
 // after them, so that waiting for the digits leaves the codes in flight.
 //
-// 64 queries, 1M records of 768 dims at 4 b/dim: 717 us on split bf16 operands,
-// 490 so; 100 queries, 250,007 records of 3,072 dims at 2 bits: 980 and 440.
-// In the first the VALU is busy 45 % of the time (half of it where passes end),
-// the LDS 43 %, the matrix cores 17 %; two waves per SIMD do not cover each
-// other's waits.  32-query tiles, with three, decode twice: 700 us.
+// Whole calls: 64 queries, 1M records of 768 dims at 4 b/dim 721 us on split bf16
+// operands, 513 so; 100 queries, 250,007 records of 3,072 dims at 2 bits 1,121 and
+// 514.  In the first the VALU is busy 42 % of the time (half of it where passes
+// end), the LDS 33 %, the matrix cores 17 % (27, 46 and 30 % in the second); two
+// waves per SIMD do not cover each other's waits.  32-query tiles, with three,
+// decode twice: 700 us.
 template <int QB, int NL>
 __global__ __launch_bounds__(256, 2) void scan_kernel(
     const u32x4* __restrict__ Qd, int nq, const float* __restrict__ qn2, const int* __restrict__ qexp,
@@ -601,11 +601,11 @@ __global__ __launch_bounds__(256, 2) void scan_kernel(
 // queries, each the operand's rows 4 q .. 4 q + 3, so that the first of a lane's
 // four sums is query lane / 16's and the others need no work.
 //
-// One query, 1M records of 1,536 dims at 4 b/dim (820 MB): 979 us on split bf16
-// operands, 278 for the whole call so (300 with four sums per lane, whose VALU
-// work is 28 % more).  The VALU is busy 58 % of that time, the texture
-// addresser 46 %; the rest is the chain of a step: LDS reads, transposition,
-// products.
+// One query, 1M records of 1,536 dims at 4 b/dim (820 MB), whole calls: 1,053 us on
+// split bf16 operands, 278 so (300 with four sums per lane, whose VALU work is 28 %
+// more); the kernel 267.  The VALU is busy 54 % of that time, the LDS 53 %, the
+// texture addresser 46 %; the rest is the chain of a step: LDS reads,
+// transposition, products.
 template <int NL, bool FOUR>
 __global__ __launch_bounds__(256, 3) void scan_few_kernel(
     const u32x4* __restrict__ Qd, int nq, const float* __restrict__ qn2, const int* __restrict__ qexp,
