@@ -99,7 +99,7 @@ template <int BI, int BJ = 2> constexpr int split_lds_floats() { return 2 * 6 * 
 
 // lds: split_lds_floats<BI>() floats, free on entry; on return free except
 // after a NORM tile (the norm hand-off leaves a barrier-protected write).
-template <int LAYOUT, bool NORM, int BI, int BJ, bool FULLB, bool REF, bool ACC64>
+template <int LAYOUT, bool NORM, int BI, int BJ, bool FULLB, bool REF, bool ACC64, bool ROWS4>
 __device__ __forceinline__ void gemm_split_tile_impl(
     bool vec, const float* __restrict__ X, int64_t n, int D, const u32x4* __restrict__ Ms,
     int k_pad, const float* __restrict__ cp, int dk, float* __restrict__ O, int64_t ld,
@@ -117,17 +117,18 @@ __device__ __forceinline__ void gemm_split_tile_impl(
     const int t = threadIdx.x;
     // What a thread stages.  QUAD: four consecutive lanes take the 16 values of a
     // row, so that a load instruction touches 16 lines instead of 64; with 128
-    // rows every thread has two of them.  Encode of 20,011 x 1536 688 -> 608 us of
-    // projection, 131,072 x 960 against references 1,643 -> 1,530; 128 x 128 tiles
-    // without references have no registers for the c that comes with it
-    // (1,350 -> 1,368) and load c as scalars.
+    // rows every thread has two of them.  The launch asks for it (ROWS4; see
+    // quad_staging): encode of 20,011 x 1536 688 -> 608 us of projection, 131,072 x
+    // 960 against references 1,643 -> 1,530; 128 x 128 tiles without references
+    // have no registers for the c that comes with it (1,350 -> 1,368) and load c
+    // as scalars.
     // Otherwise (the norm's chain takes a row's eight values of a k half in order)
     // thread t stages XS values of row t % RM in k half kh, the same for the whole
     // wave; with EVEN every thread four of the eight it loads (XL): behind a
     // branch on the thread the compiler cannot count the loads in flight and waits
     // for all of them in every step.
     constexpr bool EVEN = BJ == 1 && !REF;
-    constexpr bool QUAD = !NORM && (BI == 1 || REF);
+    constexpr bool QUAD = ROWS4 && !NORM && (BI == 1 || REF);
     constexpr int XS = EVEN || (QUAD && BI == 1) ? 4 : 8, XL = NORM ? 8 : XS;
     const int lr = QUAD ? t >> 2 : t % RM;
     const int kh = __builtin_amdgcn_readfirstlane((t / RM) & 1);
@@ -359,7 +360,7 @@ __device__ __forceinline__ void gemm_split_tile_impl(
 
 // One output tile.  ||x - c||^2 is produced by the first column tile only;
 // the k-loop is specialised so the other tiles carry none of its work.
-template <int LAYOUT, bool ACC64, int BI, bool REF = false, int BJ = 2>
+template <int LAYOUT, bool ACC64, int BI, bool REF, int BJ, bool ROWS4>
 __device__ __forceinline__ void gemm_tile(
     bool vec, const float* __restrict__ X, int64_t n, int D, const u32x4* __restrict__ Ms,
     int k_pad, const float* __restrict__ cp, int dk, float* __restrict__ O, int64_t ld,
@@ -368,13 +369,13 @@ __device__ __forceinline__ void gemm_tile(
     // 64 (w % 2) .. 64 (w % 2) + 63 of the tile) holds kept dims
     const bool fullb = BJ == 2 && tile_n * TN + 64 * int((threadIdx.x >> 6) & 1) + 32 < dk;
     if (norm2 != nullptr && tile_n == 0)
-        gemm_split_tile_impl<LAYOUT, true, BI, BJ, BJ == 2, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
+        gemm_split_tile_impl<LAYOUT, true, BI, BJ, BJ == 2, REF, ACC64, ROWS4>(vec, X, n, D, Ms, k_pad, cp, dk,
                                                                         O, ld, norm2, tile_m, tile_n, lds, R);
     else if (fullb)
-        gemm_split_tile_impl<LAYOUT, false, BI, BJ, BJ == 2, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
+        gemm_split_tile_impl<LAYOUT, false, BI, BJ, BJ == 2, REF, ACC64, ROWS4>(vec, X, n, D, Ms, k_pad, cp, dk,
                                                                          O, ld, norm2, tile_m, tile_n, lds, R);
     else
-        gemm_split_tile_impl<LAYOUT, false, BI, BJ, false, REF, ACC64>(vec, X, n, D, Ms, k_pad, cp, dk,
+        gemm_split_tile_impl<LAYOUT, false, BI, BJ, false, REF, ACC64, ROWS4>(vec, X, n, D, Ms, k_pad, cp, dk,
                                                                        O, ld, norm2, tile_m, tile_n, lds, R);
 }
 
@@ -385,7 +386,7 @@ template <bool ACC64, bool SMALL = false> constexpr int gemm_lds_size() {
     return split_lds_floats<gemm_bi<ACC64, SMALL>(), SMALL ? 1 : 2>();
 }
 
-template <bool VEC, int LAYOUT, bool ACC64, bool REF, bool SMALL>
+template <bool VEC, int LAYOUT, bool ACC64, bool REF, bool SMALL, bool ROWS4>
 __global__ __launch_bounds__(256, SMALL ? 3 : (ACC64 || REF) ? 2 : 3) void project_kernel(
     const float* __restrict__ X, int64_t n, int D, const u32x4* __restrict__ Ms, int k_pad, const float* __restrict__ cp, int dk,
     float* __restrict__ O, int64_t ld, float* __restrict__ norm2, int tiles_m, int tiles_n,
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(256, SMALL ? 3 : (ACC64 || REF) ? 2 : 3) void proje
         }
     }
     if (tile_m >= tiles_m) return;
-    gemm_tile<LAYOUT, ACC64, BI, REF, SMALL ? 1 : 2>(VEC, X, n, D, Ms, k_pad, cp, dk, O, ld, norm2, tile_m,
+    gemm_tile<LAYOUT, ACC64, BI, REF, SMALL ? 1 : 2, ROWS4>(VEC, X, n, D, Ms, k_pad, cp, dk, O, ld, norm2, tile_m,
                                                      tile_n, lds, R);
 }
 
@@ -781,7 +782,7 @@ struct GemmSet {
 };
 struct GemmArgs { GemmSet set[BATCH_MAX]; int count; int xcd_order; };
 
-template <bool ACC64, bool SMALL>
+template <bool ACC64, bool SMALL, bool ROWS4>
 __global__ __launch_bounds__(256, SMALL ? 3 : ACC64 ? 2 : 3) void grouped_gemm_kernel(const GemmArgs args) {
     constexpr int BI = gemm_bi<ACC64, SMALL>(), BJ = SMALL ? 1 : 2;
     __shared__ __attribute__((aligned(16))) float lds[gemm_lds_size<ACC64, SMALL>()];
@@ -806,11 +807,11 @@ __global__ __launch_bounds__(256, SMALL ? 3 : ACC64 ? 2 : 3) void grouped_gemm_k
     // one tile shape per launch: in a launch with FP64 totals, datasets
     // without them accumulate in FP32 on the same tile
     if (S.acc64)
-        gemm_tile<LAYOUT_TILES, ACC64, BI, false, BJ>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad, S.cp, S.dk,
+        gemm_tile<LAYOUT_TILES, ACC64, BI, false, BJ, ROWS4>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad, S.cp, S.dk,
                                           S.O, S.ld, S.norm2, tile_m, tile_n, lds,
                                           RefRows{nullptr, nullptr, 0});
     else
-        gemm_tile<LAYOUT_TILES, false, BI, false, BJ>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad, S.cp, S.dk,
+        gemm_tile<LAYOUT_TILES, false, BI, false, BJ, ROWS4>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad, S.cp, S.dk,
                                           S.O, S.ld, S.norm2, tile_m, tile_n, lds,
                                           RefRows{nullptr, nullptr, 0});
 }
@@ -901,11 +902,11 @@ __global__ __launch_bounds__(256, 2) void fused_encode_kernel(const FusedArgs ar
         for (int tile_m = tm0; tile_m < tm1; ++tile_m)
             for (int tn = 0; tn < S.tiles_n; ++tn) {
                 if (ANY64 && S.acc64)
-                    gemm_tile<LAYOUT_TILES, ANY64, BI>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad,
+                    gemm_tile<LAYOUT_TILES, ANY64, BI, false, 2, false>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad,
                                                        S.cp, S.dk, S.O, S.ld, S.norm2, tile_m, tn,
                                                        lds, RefRows{nullptr, nullptr, 0});
                 else
-                    gemm_tile<LAYOUT_TILES, false, BI>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad,
+                    gemm_tile<LAYOUT_TILES, false, BI, false, 2, false>(S.vec != 0, S.X, S.n, S.D, S.Ms, S.k_pad,
                                                        S.cp, S.dk, S.O, S.ld, S.norm2, tile_m, tn,
                                                        lds, RefRows{nullptr, nullptr, 0});
                 // the tile's LDS (and the norm hand-off) is free for the next
@@ -1865,26 +1866,57 @@ const float* dev_S(const saq_plan* p) {
 
 int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
-// 64 x 64 projection tiles where a launch has few of the larger ones, `tiles`
-// of 128 x 128, or of 64 x 128 when some rows take FP64 totals (any64): up to
-// the number that gives most of the 256 CUs one or two.  Project time with the
-// larger and with the small tiles, us (rows x dims, tiles):
-//   FP32     2000 x 768, 64: 46, 28    6000 x 768, 188: 50, 42    8000 x 768, 252: 53, 55
-//            1000 x 960, 56: 61, 33    3000 x 960, 168: 65, 52    4000 x 960, 224: 69, 67
-//   totals   1250 x 768, 100: 38, 27   4000 x 768, 315: 50, 43    5000 x 768, 395: 52, 56
-//            1000 x 1536, 160: 75, 54  2000 x 1536, 320: 90, 82   3000 x 1536, 470: 101, 115
-//   references per row (two loads per row and step, their cost doubled)
-//            1000 x 960, 56: 52, 37    2000 x 960, 112: 55, 45    4000 x 960, 224: 61, 87
-//            1200 x 1536, 190: 68, 75
-// Rows without 16-byte loads stay with the larger tiles (2000 x 333: 25, 27).
-bool small_tiles(int64_t tiles, bool any64, bool vec, bool ref) {
-    return vec && tiles < (ref ? 128 : any64 ? 360 : 224);
+// 64 x 64 projection tiles where a launch has few of the larger ones: up to three
+// of them per CU without references, where the larger ones are one or two, whose
+// k-steps then run one behind the other (720 rather than 768, as the last row and
+// column tiles are ragged).  Two per CU with long rows, whose third would stream M
+// from memory beside the others, and where their column tiles divide by eight
+// (stacked): with norms, an XCD's tiles that sum them, the longer ones, then fall
+// on the same few of its CUs.  Project time with the larger and with the small
+// tiles, us (rows x dims, small tiles):
+//   FP32     2000 x 768, 224: 44, 26    6000 x 768, 658: 46, 39    7000 x 768, 770: 46, 49
+//            1000 x 960, 224: 54, 32    3000 x 960, 658: 57, 46    3600 x 960, 798: 57, 60
+//   totals   1500 x 768, 240: 36, 25    4200 x 768, 660: 45, 41    5000 x 768, 790: 46, 54
+//            1500 x 1536, 456: 71, 58   2200 x 1536, 665: 81, 80   2600 x 1536, 779: 84, 103
+//            4200 x 640, 528 (eight columns): 39, 42; without norms 36, 30
+//            1100 x 3072, 684: 159, 205
+// With references per row (two loads per row and step, their cost doubled), by the
+// larger tiles: 1000 x 960, 56: 52, 37; 2000 x 960, 112: 55, 45; 4000 x 960, 224: 61, 87;
+// 1200 x 1536, 190: 68, 75.  Rows without 16-byte loads stay with the larger tiles
+// (2000 x 333: 25, 27).
+bool small_tiles(int64_t blocks, int ksteps, bool vec, bool stacked) {
+    return vec && blocks <= (ksteps <= 128 && !stacked ? 720 : 512);
 }
 int64_t large_tiles(const saq_plan* p, int64_t n, int bi) {
     return (n + 64 * bi - 1) / (64 * bi) * (p->layout.n_pad / TN);
 }
+
 int column_tiles(const saq_plan* p, bool small) {
     return small ? std::max(1, (p->D_kept + 63) / 64) : p->layout.n_pad / TN;
+}
+int64_t small_blocks(const saq_plan* p, int64_t n) { return (n + 63) / 64 * column_tiles(p, true); }
+
+// Whether four lanes stage a row (QUAD in the tile): with 16-byte loads only (4
+// bytes at a time it takes more instructions: 12000 x 1536 485 us, 545 so).  A
+// launch with norms ends with the tiles that sum them, which cannot; what the
+// others save then only counts over several rounds of tiles, two to a CU, or
+// where the second round is a small one.  Project time without and with
+// it, us (rows x dims, 64 x 128 tiles):
+//   norms     3600 x 960, 456: 56, 59     8500 x 768, 665: 78, 71    7500 x 1024, 708: 102, 109
+//             5000 x 1536, 790: 160, 165  20000 x 768, 1565: 149, 140
+//             1500 x 3072, 456: 178, 195  4200 x 3072, 1254: 491, 469
+//   without   5000 x 768, 395: 44, 41     3600 x 960, 456: 56, 51    2200 x 3072, 665: 281, 252
+// 64 x 64 tiles take it without norms, where a few of them leave each its CU, and
+// with long rows (rows x dims, 64 x 64 tiles):
+//   norms     1500 x 1536, 456: 58, 62    800 x 2048, 338: 67, 75    600 x 3072, 380: 154, 141
+//   without   1500 x 768, 240: 21, 19     800 x 1536, 169: 51, 36    400 x 2048, 182: 62, 48
+bool quad_staging(int64_t tiles, int ksteps, bool vec, bool ref, bool norms) {
+    if (!vec || ref) return vec;
+    if (norms) return tiles > 1024 || (ksteps <= 128 && tiles > 512 && tiles <= 704);
+    return tiles > (ksteps <= 128 ? 340 : 512);
+}
+bool quad_staging_small(int64_t blocks, int ksteps, bool ref, bool norms) {
+    return ref || !norms || ksteps > 128 || blocks <= 128;
 }
 
 saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O, int64_t ld,
@@ -1903,7 +1935,13 @@ saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O
     const bool ref = R.refs != nullptr;
     const bool vec = (p->D % 4 == 0) && ((reinterpret_cast<uintptr_t>(X) & 15) == 0) &&
                      ((reinterpret_cast<uintptr_t>(R.refs) & 15) == 0);
-    const bool small = small_tiles(large_tiles(p, n, p->acc64 ? 1 : 2), p->acc64, vec, ref);
+    const int64_t large = large_tiles(p, n, p->acc64 ? 1 : 2), blocks = small_blocks(p, n);
+    const int ksteps = p->layout.k_pad / SK;
+    const bool small = ref ? vec && large < 128
+                           : small_tiles(blocks, ksteps, vec,
+                                         norm2 != nullptr && column_tiles(p, true) % 8 == 0);
+    const bool rows4 = small ? quad_staging_small(blocks, ksteps, ref, norm2 != nullptr)
+                             : quad_staging(large, ksteps, vec, ref, norm2 != nullptr);
     const int rows = p->acc64 || small ? gemm_rows<1>() : gemm_rows<2>();
     const int tiles_m = int((n + rows - 1) / rows);
     const int tiles_n = column_tiles(p, small);
@@ -1921,12 +1959,18 @@ saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O
         slots = rows * std::max(cm, tiles_n - cm - odd) + (odd ? rows_mid : 0);
     }
     const dim3 grid(unsigned(NXCD * slots));
-#define SAQ_LAUNCH_PROJ1(V, L, A, F, S)                                                           \
-    hipLaunchKernelGGL((project_kernel<V, L, A, F, S>), grid, dim3(256), 0, st, X, n, p->D, dev_Ms(p),\
-                       p->layout.k_pad, dev_c(p), p->D_kept, O, ld, norm2, tiles_m, tiles_n, R,  \
-                       halves)
-#define SAQ_LAUNCH_PROJ(V, L, A, F) \
-    do { if (small) SAQ_LAUNCH_PROJ1(V, L, A, F, true); else SAQ_LAUNCH_PROJ1(V, L, A, F, false); } while (0)
+#define SAQ_LAUNCH_PROJ1(V, L, A, F, S, Q)                                                        \
+    hipLaunchKernelGGL((project_kernel<V, L, A, F, S, Q>), grid, dim3(256), 0, st, X, n, p->D,     \
+                       dev_Ms(p), p->layout.k_pad, dev_c(p), p->D_kept, O, ld, norm2, tiles_m,    \
+                       tiles_n, R, halves)
+    // small tiles need vec, and FP32 tiles without references never stage by four
+#define SAQ_LAUNCH_PROJ(V, L, A, F)                                     \
+    do {                                                                \
+        if (V && small && rows4) SAQ_LAUNCH_PROJ1(V, L, A, F, V, V);    \
+        else if (V && !F && small) SAQ_LAUNCH_PROJ1(V, L, A, F, (V && !F), false);  \
+        else if (V && (F || A) && rows4) SAQ_LAUNCH_PROJ1(V, L, A, F, false, (V && (F || A))); \
+        else SAQ_LAUNCH_PROJ1(V, L, A, F, false, false);                \
+    } while (0)
 #define SAQ_LAUNCH_PROJ2(V, L, F) \
     do { if (p->acc64) SAQ_LAUNCH_PROJ(V, L, true, F); else SAQ_LAUNCH_PROJ(V, L, false, F); } while (0)
     // references per row exist for the tiled (encode) and row (query) layouts
@@ -2012,6 +2056,7 @@ struct BatchPlan {
     bool fused = true;
     bool wide = false;
     bool small = false;       // grouped: 64 x 64 projection tiles
+    bool rows4 = false;       // grouped: four lanes stage a row
     bool any64 = false;       // some dataset takes FP64 k-tile totals
     size_t lds = 0;           // grouped: quantize LDS; fused: the kernel's dynamic LDS
 };
@@ -2086,16 +2131,26 @@ saq_status plan_batch(const saq_batch_item* items, int32_t count, int32_t rounds
     B.q.rounds = B.f.rounds = rounds;
     B.q.wmax = B.f.wmax = wmax;
     B.f.items = 0;
-    if (!B.fused && rows_req == 0) {
-        int64_t tiles = 0;
-        bool vec = true;
-        for (int i = 0; i < count; ++i) {
-            tiles += large_tiles(items[i].plan, items[i].n, B.bi);
-            vec = vec && (items[i].n == 0 || (items[i].plan->D % 4 == 0 &&
-                                              (reinterpret_cast<uintptr_t>(items[i].X_dev) & 15) == 0));
-        }
-        B.small = small_tiles(tiles, B.any64, vec, false);
+    int64_t tiles = 0;
+    int kmost = 0;
+    bool vec = true;
+    for (int i = 0; i < count; ++i) {
+        tiles += large_tiles(items[i].plan, items[i].n, B.bi);
+        if (items[i].n > 0) kmost = std::max(kmost, items[i].plan->layout.k_pad / SK);
+        vec = vec && (items[i].n == 0 || (items[i].plan->D % 4 == 0 &&
+                                          (reinterpret_cast<uintptr_t>(items[i].X_dev) & 15) == 0));
     }
+    int64_t blocks = 0;
+    bool stacked = false;
+    for (int i = 0; i < count; ++i) {
+        if (items[i].n == 0) continue;
+        const saq_plan* p = items[i].plan;
+        blocks += small_blocks(p, items[i].n);
+        stacked = stacked || column_tiles(p, true) % 8 == 0;
+    }
+    B.small = !B.fused && rows_req == 0 && small_tiles(blocks, kmost, vec, stacked);
+    B.rows4 = B.small ? quad_staging_small(blocks, kmost, false, true)
+                      : quad_staging(tiles, kmost, vec, false, true);
     const int rows = B.small ? 64 : 64 * B.bi;
     for (int i = 0; i < count; ++i) {
         const saq_batch_item& it = items[i];
@@ -2391,10 +2446,13 @@ saq_status saq_encode_batched(const saq_batch_item* items, int32_t count, int32_
         if (saq_status s = saq::launch_project_few(B.rows, B.q.count, LAYOUT_TILES, st); s != SAQ_OK) return s;
     } else {
         const dim3 gb(static_cast<unsigned>(B.gemm_blocks)), tb(256);
-        if (B.small && B.any64) hipLaunchKernelGGL((grouped_gemm_kernel<true, true>), gb, tb, 0, st, B.g);
-        else if (B.small) hipLaunchKernelGGL((grouped_gemm_kernel<false, true>), gb, tb, 0, st, B.g);
-        else if (B.bi == 1) hipLaunchKernelGGL((grouped_gemm_kernel<true, false>), gb, tb, 0, st, B.g);
-        else hipLaunchKernelGGL((grouped_gemm_kernel<false, false>), gb, tb, 0, st, B.g);
+        if (B.small && B.any64 && B.rows4) hipLaunchKernelGGL((grouped_gemm_kernel<true, true, true>), gb, tb, 0, st, B.g);
+        else if (B.small && B.any64) hipLaunchKernelGGL((grouped_gemm_kernel<true, true, false>), gb, tb, 0, st, B.g);
+        else if (B.small && B.rows4) hipLaunchKernelGGL((grouped_gemm_kernel<false, true, true>), gb, tb, 0, st, B.g);
+        else if (B.small) hipLaunchKernelGGL((grouped_gemm_kernel<false, true, false>), gb, tb, 0, st, B.g);
+        else if (B.bi == 1 && B.rows4) hipLaunchKernelGGL((grouped_gemm_kernel<true, false, true>), gb, tb, 0, st, B.g);
+        else if (B.bi == 1) hipLaunchKernelGGL((grouped_gemm_kernel<true, false, false>), gb, tb, 0, st, B.g);
+        else hipLaunchKernelGGL((grouped_gemm_kernel<false, false, false>), gb, tb, 0, st, B.g);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "grouped_gemm_kernel launch");

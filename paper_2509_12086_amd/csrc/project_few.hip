@@ -298,27 +298,37 @@ int64_t item_blocks(const ProjectItem& i) {
 
 namespace saq {
 
-// Where the line lies.  project_kernel's time is nearly flat while its 64 x 64
-// tiles fit the chip at once; this kernel takes 512 workgroups at a time (256
-// without FP64 totals, whose chain passes from wave to wave).  Measured, us
-// there / here, at a number of workgroups here: D = 768 with totals (608 kept)
-// 23 / 13 at 200, 26 / 23 at 500, 27 / 33 at 640; D = 1536 51 / 35 at 400, 54 / 54
-// at 760; D = 3072 97 / 95 at 690, 111 / 185 at 1,325; without totals D = 768
-// 23 / 24 at 285, 24 / 27 at 480, 26 / 38 at 705; D = 960 28 / 26 at 280, 33 / 41 at
-// 530, with references 35 / 36 at 450.  Rows without 16-byte loads have only the
-// larger tiles there, 0.7 us per k-step: D = 333 25 / 22 at 350.
+// Where the line lies: in rounds of 256 workgroups, one per CU, of which a launch
+// takes up to the number that is no slower than project_kernel's tiles.  Those
+// take about 3 us and 0.72 per k-step (0.45 in 64 x 64 tiles, 0.82 with FP32
+// accumulation), nearly flat while they fit the chip at once; a round here takes
+// 5.5 us and 0.13 per k-step.  Measured, us there / here (dims, accumulation,
+// workgroups here): D = 64 totals, 40: 6.0 / 7.0; 128, 188: 8.7 / 7.1, 276: 8.8 / 11.9; 768,
+// 200: 23 / 13, 500: 26 / 23, 640: 27 / 33; 3072, 308: 97 / 54; FP32 D = 160, 264: 12 / 16;
+// 768, 210: 23 / 13, 266: 23 / 23; 960 with references, 450: 35 / 36.
+// Rows without 16-byte loads have only the larger tiles there (1.2 us per
+// k-step), and here 32 lanes with a row each, whose lines fall together where
+// rows are a power of two apart: D = 64, 4: 6.2 / 11.6; 128, 4: 9.9 / 11.7 (one
+// row: 9.5 / 6.9); FP32 D = 160, 4: 13 / 19; 333, 225: 23 / 13, 423: 23 / 22; 256, 304: 19 / 22;
+// 512, 286: 35 / 26, 532: 35 / 38; 1536, 741: 116 / 111, 975: 115 / 140; 3072, 770: 233 / 216,
+// 1155: 233 / 333; FP32 D = 768, 490: 78 / 50, 658: 79 / 69.
+int64_t few_blocks(const ProjectItem& it) {
+    const int ksteps = it.k_pad / 16;
+    const bool vec = it.D % 4 == 0 &&
+                     ((reinterpret_cast<uintptr_t>(it.X) | reinterpret_cast<uintptr_t>(it.refs)) & 15) == 0;
+    if (ksteps < 6) return 0;
+    if (vec) return ksteps < 36 ? 256 : it.acc64 ? 512 : it.refs ? 450 : 256;
+    if (ksteps <= 10) return it.n <= 4 ? 256 : 0;
+    return ksteps < 20 ? 256 : ksteps < (it.acc64 ? 96 : 48) ? 512 : 768;
+}
 bool few_rows(const ProjectItem* items, int count) {
     double share = 0.0;
-    int64_t blocks = 0;
     for (int i = 0; i < count; ++i) {
-        const ProjectItem& it = items[i];
-        const int64_t b = item_blocks(it);
-        const bool vec = it.D % 4 == 0 &&
-                         ((reinterpret_cast<uintptr_t>(it.X) | reinterpret_cast<uintptr_t>(it.refs)) & 15) == 0;
-        blocks += b;
-        share += double(b) / (!vec ? 300 + 8 * (it.k_pad / SK) : it.acc64 ? 512 : it.refs ? 450 : 300);
+        const int64_t b = item_blocks(items[i]), most = few_blocks(items[i]);
+        if (b > most) return false;
+        share += double(b) / double(std::max<int64_t>(most, 1));
     }
-    return blocks > 0 && share <= 1.0;
+    return share > 0.0 && share <= 1.0;
 }
 
 saq_status launch_project_few(const ProjectItem* items, int count, int layout, hipStream_t st) {
