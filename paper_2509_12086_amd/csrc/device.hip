@@ -822,12 +822,14 @@ struct QuantSet {
     uint8_t* codes; int64_t code_bytes; int codes_align; float* factors;
     int64_t first_block, groups;    // groups: workgroups per segment
 };
-struct QuantArgs { QuantSet set[BATCH_MAX]; int count; int rounds; int wmax; };
+struct QuantArgs { QuantSet set[BATCH_MAX]; int64_t blocks; int count; int rounds; int wmax; };
 
 template <typename CT>
 __global__ __launch_bounds__(256) void grouped_quantize_kernel(const QuantArgs args) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int64_t b = blockIdx.x;
+    // a launch holds fewer than 2^32 threads per grid dimension: more in rows of it
+    const int64_t b = int64_t(blockIdx.y) * gridDim.x + blockIdx.x;
+    if (b >= args.blocks) return;
     int d = 0;
     while (d + 1 < args.count && b >= args.set[d + 1].first_block) ++d;
     const QuantSet& S = args.set[d];
@@ -2458,10 +2460,13 @@ saq_status saq_encode_batched(const saq_batch_item* items, int32_t count, int32_
     if (e != hipSuccess) return hip_fail(e, "grouped_gemm_kernel launch");
     if (B.few) return saq::launch_quantize_few(B.item, B.q.count, rounds, st);
     const dim3 qb(unsigned(64 * B.waves));
+    const int64_t row = std::min<int64_t>(B.quant_blocks, std::numeric_limits<uint32_t>::max() / qb.x);
+    const dim3 qg(unsigned(row), unsigned((B.quant_blocks + row - 1) / row));
+    B.q.blocks = B.quant_blocks;
     if (B.wide)
-        hipLaunchKernelGGL(grouped_quantize_kernel<uint16_t>, dim3(unsigned(B.quant_blocks)), qb, B.lds, st, B.q);
+        hipLaunchKernelGGL(grouped_quantize_kernel<uint16_t>, qg, qb, B.lds, st, B.q);
     else
-        hipLaunchKernelGGL(grouped_quantize_kernel<uint8_t>, dim3(unsigned(B.quant_blocks)), qb, B.lds, st, B.q);
+        hipLaunchKernelGGL(grouped_quantize_kernel<uint8_t>, qg, qb, B.lds, st, B.q);
     e = hipGetLastError();
     return e == hipSuccess ? SAQ_OK : hip_fail(e, "grouped_quantize_kernel launch");
 }

@@ -99,3 +99,23 @@ def test_scans_past_2_31_outputs():
     say(f"  multi-stage: stages identical {same.mean():.6f}")
     assert same.mean() >= 0.999
     assert np.max(np.abs(md - bd)[same] / scale[:, sb][same]) < TOL
+
+
+def test_grouped_batch_past_2_32_quantize_threads():
+    """67,108,901 rows of 64 one-dim segments in a grouped batch: its quantize
+    launch has a thread per vector and segment, 4.29e9, more than one grid
+    dimension holds.  Slices at both ends and around the last vectors of a first
+    row of that grid have the bytes of the same rows encoded alone.  About 75 GB
+    of device memory."""
+    d, n = 64, 2 ** 26 + 37
+    assert n * d > 2 ** 32
+    plan = saq.Plan.from_parts([1] * d, [1] * d, np.eye(d, dtype=np.float32), np.zeros(d, np.float32)).upload(0)
+    say(f"large grouped batch: {n} x {d}")
+    X = torch.randn((n, d), generator=torch.Generator("cuda").manual_seed(5), device=cuda())
+    (codes, fac), = saq.encode_batched([(plan, X)], 4, saq.BatchTuning(mode=saq.BATCH_GROUPED))
+    torch.cuda.synchronize()
+    for a, b in ((0, 300), (n // 2, n // 2 + 300), (n - 400, n - 100), (n - 100, n)):
+        c, f = saq.encode(plan, X[a:b].clone(), 4)
+        assert torch.equal(c, codes[a:b]) and torch.equal(f, fac[a:b]), (a, b)
+    del X, codes, fac
+    torch.cuda.empty_cache()
