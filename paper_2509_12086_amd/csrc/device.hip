@@ -2151,8 +2151,9 @@ saq_status plan_batch(const saq_batch_item* items, int32_t count, int32_t rounds
         stacked = stacked || column_tiles(p, true) % 8 == 0;
     }
     B.small = !B.fused && rows_req == 0 && small_tiles(blocks, kmost, vec, stacked);
-    B.rows4 = B.small ? quad_staging_small(blocks, kmost, false, true)
-                      : quad_staging(tiles, kmost, vec, false, true);
+    // small tiles of several datasets do not end with those that sum norms: three of
+    // 1900, 517 and 63 x 768 in one call 73.7 us without, 71.7 with
+    B.rows4 = B.small || quad_staging(tiles, kmost, vec, false, true);
     const int rows = B.small ? 64 : 64 * B.bi;
     for (int i = 0; i < count; ++i) {
         const saq_batch_item& it = items[i];
@@ -2448,10 +2449,8 @@ saq_status saq_encode_batched(const saq_batch_item* items, int32_t count, int32_
         if (saq_status s = saq::launch_project_few(B.rows, B.q.count, LAYOUT_TILES, st); s != SAQ_OK) return s;
     } else {
         const dim3 gb(static_cast<unsigned>(B.gemm_blocks)), tb(256);
-        if (B.small && B.any64 && B.rows4) hipLaunchKernelGGL((grouped_gemm_kernel<true, true, true>), gb, tb, 0, st, B.g);
-        else if (B.small && B.any64) hipLaunchKernelGGL((grouped_gemm_kernel<true, true, false>), gb, tb, 0, st, B.g);
-        else if (B.small && B.rows4) hipLaunchKernelGGL((grouped_gemm_kernel<false, true, true>), gb, tb, 0, st, B.g);
-        else if (B.small) hipLaunchKernelGGL((grouped_gemm_kernel<false, true, false>), gb, tb, 0, st, B.g);
+        if (B.small && B.any64) hipLaunchKernelGGL((grouped_gemm_kernel<true, true, true>), gb, tb, 0, st, B.g);
+        else if (B.small) hipLaunchKernelGGL((grouped_gemm_kernel<false, true, true>), gb, tb, 0, st, B.g);
         else if (B.bi == 1 && B.rows4) hipLaunchKernelGGL((grouped_gemm_kernel<true, false, true>), gb, tb, 0, st, B.g);
         else if (B.bi == 1) hipLaunchKernelGGL((grouped_gemm_kernel<true, false, false>), gb, tb, 0, st, B.g);
         else hipLaunchKernelGGL((grouped_gemm_kernel<false, false, false>), gb, tb, 0, st, B.g);
