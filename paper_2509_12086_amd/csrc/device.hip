@@ -1871,23 +1871,24 @@ int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 // 64 x 64 projection tiles where a launch has few of the larger ones: up to three
 // of them per CU without references, where the larger ones are one or two, whose
 // k-steps then run one behind the other (720 rather than 768, as the last row and
-// column tiles are ragged).  Two per CU with long rows, whose third would stream M
-// from memory beside the others, and where their column tiles divide by eight
-// (stacked): with norms, an XCD's tiles that sum them, the longer ones, then fall
-// on the same few of its CUs.  Project time with the larger and with the small
-// tiles, us (rows x dims, small tiles):
+// column tiles are ragged).  Two per CU with short rows, which are over before it
+// counts, with long ones, whose third would stream M from memory beside the
+// others, and where their column tiles divide by eight (stacked): with norms, an
+// XCD's tiles that sum them, the longer ones, then fall on the same few of its
+// CUs.  Project time with the larger and with the small tiles, us (rows x dims,
+// small tiles):
 //   FP32     2000 x 768, 224: 44, 26    6000 x 768, 658: 46, 39    7000 x 768, 770: 46, 49
 //            1000 x 960, 224: 54, 32    3000 x 960, 658: 57, 46    3600 x 960, 798: 57, 60
 //   totals   1500 x 768, 240: 36, 25    4200 x 768, 660: 45, 41    5000 x 768, 790: 46, 54
 //            1500 x 1536, 456: 71, 58   2200 x 1536, 665: 81, 80   2600 x 1536, 779: 84, 103
 //            4200 x 640, 528 (eight columns): 39, 42; without norms 36, 30
-//            1100 x 3072, 684: 159, 205
+//            1100 x 3072, 684: 159, 205  20000 x 128, 626: 12.5, 13.4
 // With references per row (two loads per row and step, their cost doubled), by the
 // larger tiles: 1000 x 960, 56: 52, 37; 2000 x 960, 112: 55, 45; 4000 x 960, 224: 61, 87;
 // 1200 x 1536, 190: 68, 75.  Rows without 16-byte loads stay with the larger tiles
 // (2000 x 333: 25, 27).
-bool small_tiles(int64_t blocks, int ksteps, bool vec, bool stacked) {
-    return vec && blocks <= (ksteps <= 128 && !stacked ? 720 : 512);
+bool small_tiles(int64_t blocks, int kleast, int kmost, bool vec, bool stacked) {
+    return vec && blocks <= (kleast >= 16 && kmost <= 128 && !stacked ? 720 : 512);
 }
 int64_t large_tiles(const saq_plan* p, int64_t n, int bi) {
     return (n + 64 * bi - 1) / (64 * bi) * (p->layout.n_pad / TN);
@@ -1940,7 +1941,7 @@ saq_status launch_project(const saq_plan* p, const float* X, int64_t n, float* O
     const int64_t large = large_tiles(p, n, p->acc64 ? 1 : 2), blocks = small_blocks(p, n);
     const int ksteps = p->layout.k_pad / SK;
     const bool small = ref ? vec && large < 128
-                           : small_tiles(blocks, ksteps, vec,
+                           : small_tiles(blocks, ksteps, ksteps, vec,
                                          norm2 != nullptr && column_tiles(p, true) % 8 == 0);
     const bool rows4 = small ? quad_staging_small(blocks, ksteps, ref, norm2 != nullptr)
                              : quad_staging(large, ksteps, vec, ref, norm2 != nullptr);
@@ -2143,14 +2144,16 @@ saq_status plan_batch(const saq_batch_item* items, int32_t count, int32_t rounds
                                           (reinterpret_cast<uintptr_t>(items[i].X_dev) & 15) == 0));
     }
     int64_t blocks = 0;
+    int kleast = std::numeric_limits<int>::max();
     bool stacked = false;
     for (int i = 0; i < count; ++i) {
         if (items[i].n == 0) continue;
         const saq_plan* p = items[i].plan;
         blocks += small_blocks(p, items[i].n);
+        kleast = std::min(kleast, p->layout.k_pad / SK);
         stacked = stacked || column_tiles(p, true) % 8 == 0;
     }
-    B.small = !B.fused && rows_req == 0 && small_tiles(blocks, kmost, vec, stacked);
+    B.small = !B.fused && rows_req == 0 && small_tiles(blocks, kleast, kmost, vec, stacked);
     // small tiles of several datasets do not end with those that sum norms: three of
     // 1900, 517 and 63 x 768 in one call 73.7 us without, 71.7 with
     B.rows4 = B.small || quad_staging(tiles, kmost, vec, false, true);
